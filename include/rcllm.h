@@ -33,6 +33,7 @@
  * selected rows, Sec. III-C.2b), with random-weight decoder layers:
  *
  *   rc_gemm_bf16                Y = X W^T (+ residual) projections
+ *   rc_gemm_bf16_ws             the same with a workspace for split sums
  *   rc_rmsnorm                  RMSNorm of rows
  *   rc_qkv_rope                 split a QKV projection, rotate q and k to
  *                               their positions, write q/k/v at those
@@ -441,6 +442,21 @@ int rc_segments_with_window(const rc_segment* segs_in, int32_t B, int32_t S, int
  * multiple of 8, y overlapping x, w or residual. */
 int rc_gemm_bf16(int64_t M, int32_t n, int32_t k, const void* x, const void* w,
                  const void* residual, void* y, hipStream_t stream);
+
+/* rc_gemm_bf16 with a workspace for fp32 partial sums: where M x n has too few
+ * tiles to occupy the GPU, the sum over k is split over workgroups and the
+ * partial sums are added in a fixed order (deterministic; the order depends on
+ * M, n, k and on whether workspace_bytes suffices). workspace: device memory,
+ * 16-byte aligned, of rc_gemm_workspace_bytes(M, n, k) bytes (host function; 0
+ * where no split pays off, at most 128 MiB), used until `stream` has run the
+ * call; its contents are unspecified afterwards. NULL or a smaller one: the
+ * call uses what fits.
+ * Errors: those of rc_gemm_bf16; INVALID_ARG for workspace_bytes < 0 or a
+ * workspace overlapping x, w, y or residual. */
+int64_t rc_gemm_workspace_bytes(int64_t M, int32_t n, int32_t k);
+int rc_gemm_bf16_ws(int64_t M, int32_t n, int32_t k, const void* x, const void* w,
+                    const void* residual, void* y, void* workspace, int64_t workspace_bytes,
+                    hipStream_t stream);
 
 /* RMSNorm of M rows of width H (bf16 device tensors x, y [M, H], gamma [H]):
  *   y = x / sqrt(mean(x^2) + eps) * gamma   (fp32 statistics, RNE to bf16).

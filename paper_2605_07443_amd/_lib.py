@@ -26,7 +26,7 @@ EXPORTS = ("rc_rope_table", "rc_kv_assemble", "rc_rerope", "rc_select_tokens",
            "rc_select_tokens_eq3", "rc_paged_attention", "rc_segments_with_window",
            "rc_kv_gather_tokens", "rc_gemm_bf16", "rc_rmsnorm", "rc_qkv_rope", "rc_silu_mul",
            "rc_gather_rows", "rc_kv_assemble_vref", "rc_select_tokens_vref",
-           "rc_selective_attention_vref",
+           "rc_selective_attention_vref", "rc_gemm_workspace_bytes", "rc_gemm_bf16_ws",
            "rc_status_string", "rc_last_error")
 
 
@@ -77,6 +77,8 @@ def load() -> ctypes.CDLL:
                                       vp, i32, vp]
     i64 = ctypes.c_int64
     L.rc_gemm_bf16.argtypes = [i64, i32, i32, vp, vp, vp, vp, vp]
+    L.rc_gemm_workspace_bytes.argtypes = [i64, i32, i32]
+    L.rc_gemm_bf16_ws.argtypes = [i64, i32, i32, vp, vp, vp, vp, vp, i64, vp]
     L.rc_rmsnorm.argtypes = [i32, i32, vp, vp, f32, vp, vp]
     L.rc_qkv_rope.argtypes = [P(RcShape), vp, vp, i32, vp, vp, i32, vp, vp, vp, vp]
     L.rc_silu_mul.argtypes = [i64, i32, vp, vp, vp]
@@ -88,6 +90,7 @@ def load() -> ctypes.CDLL:
     for name in EXPORTS:
         if name not in ("rc_status_string", "rc_last_error"):
             getattr(L, name).restype = ctypes.c_int
+    L.rc_gemm_workspace_bytes.restype = i64
     L.rc_status_string.argtypes = [ctypes.c_int]
     L.rc_status_string.restype = ctypes.c_char_p
     L.rc_last_error.argtypes = []

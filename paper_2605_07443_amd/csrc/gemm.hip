@@ -1,20 +1,19 @@
 // Projections of a decoder layer (QKV, O, gate/up, down) for the multi-layer
 // path: Y[M, n] = X[M, k] W[n, k]^T (+ residual), bf16 storage, fp32
-// accumulation on the matrix cores (v_mfma_f32_16x16x32_bf16).
+// accumulation on the matrix cores.
 //
 // Both operands are k-contiguous, which is the native operand order of the
 // MFMA: a lane's fragment is 8 consecutive k of one W row (the MFMA's A
 // operand) or of one X row (its B operand). With W as A the accumulators hold
 // Y^T, so each lane ends with 4 consecutive outputs of one row and the
-// epilogue stores 8-byte packs instead of single values. A workgroup computes
-// a 128 x 128 tile of Y with 4 waves of 64 x 64 (4 x 4 accumulator blocks
-// each); X and W tiles of 64 k stream through double-buffered LDS (rows
-// padded to 144 bytes, so the 16-byte fragment reads of 16 consecutive rows
-// are conflict-free), with the next tile's global loads in flight during the
-// MFMAs. Consecutive workgroups walk the 8 row tiles of a group before moving
-// to the next column tile; as workgroups are dealt to the 8 XCDs in turn,
-// each XCD keeps one row tile of X in its L2 while the column tiles of W
-// stream past.
+// epilogue stores 8-byte packs instead of single values.
+//
+//   gemm_bf16_tile_kernel  k % 64 == 0: tiles of 256 x 256, 128 x 128 or
+//                          64 x 128, optionally split over k (fp32 partial
+//                          sums in a caller's workspace, added in order by
+//                          gemm_reduce_kernel)
+//   gemm_bf16_kernel       any other k, or operands that are not 16-byte
+//                          aligned: 128 x 128 tiles staged through registers
 #include <type_traits>
 
 #include "rc_common.h"
@@ -26,7 +25,8 @@ using u32x4 = u32x4_t;
 constexpr int kGThreads = 256;
 constexpr int kGM = 128, kGN = 128, kGK = 64;
 constexpr int kGPad = 8;
-constexpr int kGGroup = 8;  // row tiles per ordering group
+constexpr int kGGroup = 4;  // row tiles per ordering group
+constexpr int kGXcds = 8;
 constexpr int kGUnits = kGK / 8;                              // 16-byte units per tile row
 constexpr int kGPer = kGM * kGUnits / kGThreads;              // units per thread per operand (4)
 
@@ -170,248 +170,502 @@ void gemm_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict
   store_wave_tile(acc, res, y, M, n, m0 + wm, n0 + wn, c16, q4, vec != 0);
 }
 
-// Large tiles for k % 64 == 0: a 256 x 256 tile per workgroup of 8 waves,
-// each 128 x 64 (8 x 4 accumulator blocks), two waves per SIMD. X and W tiles
-// of 64 k go straight from global memory into LDS (global_load_lds_dwordx4,
-// 1 KB = 8 rows of 128 B per wave instruction), so the 16-byte chunks of a
-// row are XOR-swizzled instead of padded: row r keeps data chunk c at chunk
+// Order of the tiles: workgroups are dealt to the 8 XCDs in turn, so XCD c gets
+// ids c, c + 8, ...; they take a contiguous range of the tile order (bijective
+// for any count), in which kGGroup row tiles are walked before the next column
+// tile: the tiles that one XCD works on together form a block of row tiles x
+// column tiles, so that its L2 serves both operands several times.
+__device__ __forceinline__ int64_t gemm_tile_order(int64_t id, int64_t tiles) {
+  const int64_t per = tiles / kGXcds, rem = tiles % kGXcds;
+  const int64_t xcd = id % kGXcds, i = id / kGXcds;
+  return xcd * per + min(xcd, rem) + i;
+}
+
+// Four consecutive outputs of one row at column gc (the residual is added in
+// fp32 before the single rounding), as one 8-byte pack when the layout allows
+// it (vec: n % 4 == 0 and 8-byte aligned y and residual), else one by one.
+__device__ __forceinline__ void store_outputs(f32x4 v, const uint16_t* res, uint16_t* y, int gc, int n, int vec) {
+  if (vec && gc + 3 < n) {
+    if (res) {
+      const u32x2 rr = *reinterpret_cast<const u32x2*>(res + gc);
+      v[0] += bf16_to_f32(static_cast<uint16_t>(rr[0]));
+      v[1] += bf16_to_f32(static_cast<uint16_t>(rr[0] >> 16));
+      v[2] += bf16_to_f32(static_cast<uint16_t>(rr[1]));
+      v[3] += bf16_to_f32(static_cast<uint16_t>(rr[1] >> 16));
+    }
+    const u32x2 o = {static_cast<uint32_t>(f32_to_bf16(v[0])) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16),
+                     static_cast<uint32_t>(f32_to_bf16(v[2])) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16)};
+    *reinterpret_cast<u32x2*>(y + gc) = o;
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (gc + r >= n) continue;
+      float t = v[r];
+      if (res) t += bf16_to_f32(res[gc + r]);
+      y[gc + r] = f32_to_bf16(t);
+    }
+  }
+}
+
+__device__ __forceinline__ void store_partial(f32x4 v, float* p, int gc, int n, int vec) {
+  if (vec && gc + 3 < n) {
+    *reinterpret_cast<f32x4*>(p + gc) = v;
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (gc + r < n) p[gc + r] = v[r];
+  }
+}
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+// Tiles of BM x BN for k % 64 == 0 (16-byte aligned operands): waves of WM x WN
+// (MI x NJ blocks of v_mfma_f32_32x32x16_bf16). X and W tiles of 64 k go
+// straight from global memory into LDS (global_load_lds_dwordx4, 1 KB = 8 rows
+// of 128 B per wave instruction), so the 16-byte chunks of a row are
+// XOR-swizzled instead of padded: row r keeps data chunk c at chunk
 // c ^ ((r >> 1) & 7), which puts the fragment reads of 16 consecutive rows on
-// 16 distinct (bank half, chunk) pairs. The two LDS buffers are separate
-// objects and every k tile knows its buffer at compile time, so loading one
-// never waits on reading the other. Rows past M or n repeat the last row
-// (finite values whose products are never stored).
-constexpr int kBThreads = 512;
-constexpr int kBM = 256, kBN = 256;
-struct GemmBuf {
-  uint16_t a[kBM * kGK];
-  uint16_t b[kBN * kGK];
+// 16 distinct (bank half, chunk) pairs (no bank conflicts measured). Rows past
+// M or n repeat the last row (finite values whose products are never stored).
+//
+// The k loop keeps the matrix cores fed across its one barrier per 64 k: the
+// fragments of the next 16 k are read from LDS while the products of the
+// current 16 k run, so both sides of the barrier begin with products whose
+// operands are in registers, and the tile after next is loaded, one load after
+// each product, into the buffer that the barrier has just released. One loop
+// body with the buffer as a run-time offset keeps the accumulators in place
+// (194 registers for 256 x 256; two unrolled bodies with branches spilled
+// 280). What bounds it: with random operands the chip lowers its clock (1.6
+// GHz measured at 73% matrix-core utilisation, 2.4 GHz with zeros), so the
+// tile with the fewest LDS bytes per product is the fastest: 8192^3 at 1300
+// TFLOP/s with 256 x 256 tiles of 128 x 64 waves, 1010-1100 with 64 x 64 waves
+// (the kernel before: 1180); a ring of five 32-k stages (twice the load lead,
+// twice the barriers) reached 1240, 4 waves of 128 x 128 reached 1250.
+// SPLIT: blockIdx.y is the split s of S; k tiles [s KT / S, (s + 1) KT / S) are
+// summed and the fp32 partial sums go to part[s] (gemm_reduce_kernel adds them).
+template <int BM_, int BN_, int WM_, int WN_>
+struct GemmCfg {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
+  static constexpr int Waves = (BM / WM) * (BN / WN);
+  static constexpr int Threads = Waves * 64;
+  static constexpr int MI = WM / 32, NJ = WN / 32;
+  static constexpr int XL = BM / 8 / Waves, WL = BN / 8 / Waves;  // tile loads per wave
+  static_assert(XL * Waves * 8 == BM && WL * Waves * 8 == BN, "whole loads per wave");
 };
 
-__global__ __launch_bounds__(kBThreads) __attribute__((amdgpu_waves_per_eu(2)))
-void gemm_bf16_big_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
-                          const uint16_t* __restrict__ res, uint16_t* __restrict__ y, int64_t M,
-                          int n, int k, int tiles_m, int tiles_n, int vec) {
-  __shared__ GemmBuf s0, s1;
-  const int64_t bid = blockIdx.x;
+template <typename C>
+struct GemmTile {
+  alignas(16) uint16_t x[2][C::BM * kGK];
+  alignas(16) uint16_t w[2][C::BN * kGK];
+};
+
+// One global->LDS load (16 bytes per lane, 1 KB per wave) from a wave-uniform
+// base plus a 32-bit per-lane byte offset into the LDS bytes at lds_addr
+// (wave-uniform). As assembly the compiler does not track it; the kernel waits
+// for it with an explicit vmcnt wait before its barrier. M0 is restored.
+__device__ __forceinline__ void gemm_dma16(uint32_t lds_addr, const void* gbase, uint32_t goff) {
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "s"(lds_addr), "v"(goff), "s"(gbase)
+      : "memory");
+}
+
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
+      (const __attribute__((address_space(3))) void*)(p)));
+}
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+template <typename C, bool SPLIT>
+__global__ __launch_bounds__(C::Threads) __attribute__((amdgpu_waves_per_eu(2)))
+void gemm_bf16_tile_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
+                           const uint16_t* __restrict__ res, uint16_t* __restrict__ y,
+                           float* __restrict__ part, int64_t M, int n, int k, int tiles_m,
+                           int tiles_n, int vec) {
+  __shared__ GemmTile<C> sm;
+  constexpr int MI = C::MI, NJ = C::NJ;
+  // ---- tile of this workgroup
+  const int64_t tiles = static_cast<int64_t>(tiles_m) * tiles_n;
+  const int64_t bid = gemm_tile_order(blockIdx.x, tiles);
   const int64_t per_group = static_cast<int64_t>(kGGroup) * tiles_n;
   const int64_t grp = bid / per_group;
   const int64_t in = bid - grp * per_group;
   const int64_t first_m = grp * kGGroup;
   const int64_t gm = min(static_cast<int64_t>(kGGroup), tiles_m - first_m);
-  const int64_t tm = first_m + in % gm;
-  const int tn = static_cast<int>(in / gm);
-  const int64_t m0 = tm * kBM;
-  const int n0 = tn * kBN;
+  const int64_t m0 = (first_m + in % gm) * C::BM;
+  const int n0 = static_cast<int>(in / gm) * C::BN;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int c16 = lane & 15;
-  const int q4 = lane >> 4;
-  const int wm = (wave >> 2) * 128;
-  const int wn = (wave & 3) * 64;
-  const int n_kt = k / kGK;
-
-  // wave w fills rows 32w .. 32w+31 of both tiles, 8 rows per instruction
-  auto issue = [&](int kt, auto buf_tag) {
-    GemmBuf& dst = decltype(buf_tag)::value ? s1 : s0;
-    const int ch = lane & 7;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = wave * 32 + j * 8 + (lane >> 3);
-      const int dch = ch ^ ((row >> 1) & 7);
-      const int64_t gr = min(m0 + row, M - 1);
-      const int gc = min(n0 + row, n - 1);
-      const int kk = kt * kGK + dch * 8;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(x + gr * k + kk),
-                                       (__attribute__((address_space(3))) void*)(&dst.a[(wave * 32 + j * 8) * kGK]),
-                                       16, 0, 0);
-      __builtin_amdgcn_global_load_lds(
-          (const __attribute__((address_space(1))) void*)(w + static_cast<int64_t>(gc) * k + kk),
-          (__attribute__((address_space(3))) void*)(&dst.b[(wave * 32 + j * 8) * kGK]), 16, 0, 0);
-    }
-  };
-
-  f32x4 acc[8][4];
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  auto compute = [&](auto buf_tag) {
-    const GemmBuf& src = decltype(buf_tag)::value ? s1 : s0;
-#pragma unroll
-    for (int ks = 0; ks < kGK / 32; ++ks) {
-      const int u = ks * 4 + q4;
-      bf16x8 fb[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int rb = wn + j * 16 + c16;
-        fb[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(
-                                               &src.b[rb * kGK + ((u ^ ((rb >> 1) & 7)) * 8)]));
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int ra = wm + i * 16 + c16;
-        const bf16x8 fa = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(
-                                                       &src.a[ra * kGK + ((u ^ ((ra >> 1) & 7)) * 8)]));
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa, acc[i][j], 0, 0, 0);
-      }
-    }
-  };
-  using B0 = std::integral_constant<int, 0>;
-  using B1 = std::integral_constant<int, 1>;
-
-  issue(0, B0{});
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  int kt = 0;
-  // the scheduling barriers keep each tile's loads ahead of the MFMAs of the
-  // tile before it: left free, the scheduler sinks them to the end of that
-  // tile (less address-register pressure), where the wait right after them
-  // exposes the whole memory latency
-  for (; kt + 1 < n_kt; kt += 2) {
-    issue(kt + 1, B1{});
-    __builtin_amdgcn_sched_barrier(0);
-    compute(B0{});
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (kt + 2 < n_kt) issue(kt + 2, B0{});
-    __builtin_amdgcn_sched_barrier(0);
-    compute(B1{});
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r32 = lane & 31;
+  const int hi = lane >> 5;
+  const int wm = (wave / (C::BN / C::WN)) * C::WM;
+  const int wn = (wave % (C::BN / C::WN)) * C::WN;
+  const int KT = k / kGK;
+  int kt0 = 0, kt1 = KT;
+  if constexpr (SPLIT) {
+    kt0 = static_cast<int>(static_cast<int64_t>(blockIdx.y) * KT / gridDim.y);
+    kt1 = static_cast<int>(static_cast<int64_t>(blockIdx.y + 1) * KT / gridDim.y);
   }
-  if (kt < n_kt) compute(B0{});
-  store_wave_tile(acc, res, y, M, n, m0 + wm, n0 + wn, c16, q4, vec != 0);
+
+  // ---- tile loads: wave w fills rows 8 (w XL + j) .. + 7 of the X tile (and
+  // likewise of the W tile); lane l writes chunk l % 8 of row l / 8 of them
+  uint32_t xoff[C::XL], woff[C::WL];
+#pragma unroll
+  for (int j = 0; j < C::XL; ++j) {
+    const int row = (wave * C::XL + j) * 8 + (lane >> 3);
+    const int64_t gr = min(m0 + row, M - 1) - m0;
+    xoff[j] = static_cast<uint32_t>((gr * k + (((lane & 7) ^ ((row >> 1) & 7)) * 8)) * 2);
+  }
+#pragma unroll
+  for (int j = 0; j < C::WL; ++j) {
+    const int row = (wave * C::WL + j) * 8 + (lane >> 3);
+    const int gr = min(n0 + row, n - 1) - n0;
+    woff[j] = static_cast<uint32_t>((static_cast<int64_t>(gr) * k + (((lane & 7) ^ ((row >> 1) & 7)) * 8)) * 2);
+  }
+  const char* xb = reinterpret_cast<const char*>(x + m0 * k);
+  const char* wb = reinterpret_cast<const char*>(w + static_cast<int64_t>(n0) * k);
+  const uint32_t lx = lds_offset(&sm.x[0][0]) + wave * C::XL * 1024;
+  const uint32_t lw = lds_offset(&sm.w[0][0]) + wave * C::WL * 1024;
+  // load j of this wave's XL + WL loads of tile kt into buffer buf
+  auto issue1 = [&](int kt, int buf, auto J) __attribute__((always_inline)) {
+    constexpr int j = decltype(J)::value;
+    const int64_t kb = static_cast<int64_t>(kt) * (kGK * 2);
+    if constexpr (j < C::XL) gemm_dma16(lx + buf * (C::BM * kGK * 2) + j * 1024, xb + kb, xoff[j]);
+    else gemm_dma16(lw + buf * (C::BN * kGK * 2) + (j - C::XL) * 1024, wb + kb, woff[j - C::XL]);
+  };
+  auto issue = [&](int kt, int buf) __attribute__((always_inline)) {
+    static_for<0, C::XL + C::WL>([&](auto J) { issue1(kt, buf, J); });
+  };
+
+  // ---- fragments of 16 k (step ks of a tile): lane holds row r32 of a 32-row
+  // block, 8 consecutive k at 16 ks + 8 hi
+  struct Frag {
+    bf16x8 x[MI], w[NJ];
+  };
+  const int swz = (r32 >> 1) & 7;
+  auto read1 = [&](Frag& f, int ks, int buf, auto R) __attribute__((always_inline)) {
+    constexpr int r = decltype(R)::value;   // the W fragments, then the X fragments
+    const int ch = ((ks * 2 + hi) ^ swz) * 8;
+    if constexpr (r < NJ)
+      f.w[r] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(&sm.w[buf][(wn + r * 32 + r32) * kGK + ch]));
+    else
+      f.x[r - NJ] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(&sm.x[buf][(wm + (r - NJ) * 32 + r32) * kGK + ch]));
+  };
+  f32x16 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  // One step: the products of fragments f, and after each of them one read of
+  // the next step's fragments g (READ) and one load of a later tile (LOAD). The
+  // order is pinned: left free, the compiler gathers the loads in one place,
+  // where every wave of the workgroup leaves the matrix cores idle at once.
+  auto step = [&](const Frag& f, Frag& g, int ks, int buf, int kt_load, int buf_load, auto rd, auto ld)
+      __attribute__((always_inline)) {
+    constexpr int P = MI * NJ, NR = MI + NJ, NL = C::XL + C::WL, PR = (NR + P - 1) / P;
+    static_for<0, P>([&](auto I) {
+      constexpr int p = decltype(I)::value;
+      acc[p / NJ][p % NJ] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[p % NJ], f.x[p / NJ], acc[p / NJ][p % NJ], 0, 0, 0);
+      if constexpr (decltype(rd)::value) {
+        static_for<(p * PR < NR ? p * PR : NR), ((p + 1) * PR < NR ? (p + 1) * PR : NR)>([&](auto R) { read1(g, ks, buf, R); });
+      }
+      if constexpr (decltype(ld)::value) {
+        static_for<p * NL / P, (p + 1) * NL / P>([&](auto J) { issue1(kt_load, buf_load, J); });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // the next tile's loads have landed and every wave has read the current one
+  auto turn = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using Yes = std::true_type;
+  using No = std::false_type;
+  if (kt0 < kt1) {
+    Frag f0, f1;
+    issue(kt0, 0);
+    turn();
+    issue(min(kt0 + 1, kt1 - 1), 1);
+    int cur = 0;
+    static_for<0, MI + NJ>([&](auto R) { read1(f0, 0, 0, R); });
+    for (int kt = kt0; kt + 1 < kt1; ++kt) {
+      step(f0, f1, 1, cur, 0, 0, Yes{}, No{});
+      step(f1, f0, 2, cur, 0, 0, Yes{}, No{});
+      step(f0, f1, 3, cur, 0, 0, Yes{}, No{});
+      turn();
+      // past the last tile the loads repeat it, into a buffer that is not read again
+      step(f1, f0, 0, cur ^ 1, min(kt + 2, kt1 - 1), cur, Yes{}, Yes{});
+      cur ^= 1;
+    }
+    step(f0, f1, 1, cur, 0, 0, Yes{}, No{});
+    step(f1, f0, 2, cur, 0, 0, Yes{}, No{});
+    step(f0, f1, 3, cur, 0, 0, Yes{}, No{});
+    step(f1, f0, 0, cur, 0, 0, No{}, No{});
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load into LDS outlives the workgroup
+  }
+
+  // ---- a lane holds column r32 (row of Y) of each block and, for g < 4, rows
+  // 8 g + 4 hi .. + 3 (consecutive outputs)
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    const int64_t gr = m0 + wm + i * 32 + r32;
+    if (gr >= M) continue;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int gc = n0 + wn + j * 32 + g * 8 + hi * 4;
+        const f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+        if constexpr (SPLIT) store_partial(v, part + (static_cast<int64_t>(blockIdx.y) * M + gr) * n, gc, n, vec);
+        else store_outputs(v, res ? res + gr * n : nullptr, y + gr * n, gc, n, vec);
+      }
+  }
 }
 
-// Row tail of fewer than 256 rows left by the 256 x 256 kernel, for shapes
-// where that tail would otherwise run as a few half-empty 128 x 128
-// workgroups through the whole k loop (a second round as long as the first):
-// split-K. Workgroup (column tile, row tile, split s) computes a 64 x 64 tile
-// over the k tiles [s * KT / S, (s + 1) * KT / S) and writes its fp32 partial
-// sums to part[s]; gemm_tail_reduce_kernel then adds the S partials in order
-// of s and the residual, and rounds once. The partials live in the first rows
-// of y, which the 256 x 256 kernel overwrites afterwards on the same stream,
-// so the call allocates nothing. Four waves, each 16 columns (W rows, read
-// straight from global memory one k tile ahead) x the 64 rows (X tile staged
-// in LDS); operand roles and fragment layout as in the kernels above.
-constexpr int kSThreads = 256;
-constexpr int kSM = 64, kSN = 64;
-constexpr int kSPer = kSM * kGUnits / kSThreads;   // X units per thread per k tile (2)
+// y[e] = bf16(sum over s of part[s][e] (+ residual[e])), s in order, count values;
+// four consecutive values per thread (vec: count % 4 == 0 and aligned y, residual)
+__global__ __launch_bounds__(256)
+void gemm_reduce_kernel(const float* __restrict__ part, const uint16_t* __restrict__ res,
+                        uint16_t* __restrict__ y, int64_t count, int splits, int vec) {
+  const int64_t e = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * 4;
+  if (e >= count) return;
+  if (vec) {
+    f32x4 v = *reinterpret_cast<const f32x4*>(part + e);
+#pragma unroll 4
+    for (int s = 1; s < splits; ++s) v += *reinterpret_cast<const f32x4*>(part + s * count + e);
+    store_outputs(v, res ? res + e : nullptr, y + e, 0, 4, 1);
+    return;
+  }
+  for (int64_t i = e; i < min(e + 4, count); ++i) {
+    float v = part[i];
+    for (int s = 1; s < splits; ++s) v += part[s * count + i];
+    if (res) v += bf16_to_f32(res[i]);
+    y[i] = f32_to_bf16(v);
+  }
+}
 
-struct GemmSplitSmem {
-  uint16_t x[2][kSM][kGK + kGPad];
+// ------------------------------------------------------------------- plan
+
+constexpr int kBM = 256, kBN = 256;  // largest tile
+constexpr int kSM = 64, kSN = 128;   // smallest tile
+constexpr int kSThreads = 256;
+using CfgBig = GemmCfg<kBM, kBN, 128, 64>;
+using CfgMid = GemmCfg<kGM, kGN, 64, 64>;
+using CfgSmall = GemmCfg<kSM, kSN, 64, 32>;
+static_assert(CfgSmall::Threads == kSThreads, "small tile threads");
+
+constexpr int64_t kGMaxWorkspace = 128ll << 20;  // bytes of fp32 partial sums at most
+constexpr int kGMaxSplits = 16;
+constexpr int kGMaxK = 1 << 22;  // 32-bit byte offsets within a tile's rows
+
+// How M rows are computed: one tile shape, S splits of k.
+struct GemmPart {
+  int cfg = 0;      // 0: 256 x 256, 1: 128 x 128, 2: 64 x 128
+  int splits = 1;
 };
 
-__global__ __launch_bounds__(kSThreads)
-void gemm_bf16_splitk_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
-                             float* __restrict__ part, int64_t M, int n, int k, int splits) {
-  __shared__ GemmSplitSmem sm;
-  const int n0 = blockIdx.x * kSN;
-  const int64_t m0 = static_cast<int64_t>(blockIdx.y) * kSM;
-  const int s = blockIdx.z;
+// Estimated time of a part in ns. A k tile (64 k) of a tile shape takes
+// kTile[shape][r - 1] when r workgroups share each compute unit (256, 512 or
+// 768 workgroups resident), between those by interpolation; splitting adds the
+// traffic of the partial sums; and no call is faster than reading W. The
+// constants are a least-squares fit to 28 shapes x 15 (shape, split) pairs
+// (M = 48 .. 4160 against the four projections of a 4096 / 14336 layer): the
+// pair with the least estimate is within 5% of the fastest measured one on
+// each of them, 0.3% on average.
+double gemm_estimate(const GemmPart& p, int64_t M, int n, int k) {
+  constexpr int kBm[3] = {256, 128, 64}, kBn[3] = {256, 128, 128}, kOcc[3] = {1, 2, 3};
+  constexpr double kTile[3][3] = {{1420, 0, 0}, {690, 930, 0}, {480, 760, 980}};
+  constexpr double kIdle = 0.8;          // k tile time of a nearly empty chip over that of one workgroup per CU
+  constexpr double kFixed = 6600;        // prologue, epilogue, launch
+  constexpr double kSplitValue = 1.5e-3; // ns per partial sum written and read
+  constexpr double kStream = 5460;       // bytes of W per ns
+  const int64_t tiles = ((M + kBm[p.cfg] - 1) / kBm[p.cfg]) * ((n + kBn[p.cfg] - 1) / kBn[p.cfg]);
+  const int64_t wgs = tiles * p.splits;
+  const int occ = kOcc[p.cfg];
+  const int64_t full = wgs / (256 * occ), rest = wgs % (256 * occ);
+  double t = static_cast<double>(full) * kTile[p.cfg][occ - 1];
+  if (rest) {
+    const int i = static_cast<int>((rest + 255) / 256) - 1;
+    const double lo = i > 0 ? kTile[p.cfg][i - 1] : kTile[p.cfg][0] * kIdle;
+    t += lo + (kTile[p.cfg][i] - lo) * (rest / 256.0 - i);
+  }
   const int KT = k / kGK;
-  const int kt0 = static_cast<int>(static_cast<int64_t>(s) * KT / splits);
-  const int kt1 = static_cast<int>(static_cast<int64_t>(s + 1) * KT / splits);
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int c16 = lane & 15;
-  const int q4 = lane >> 4;
-  const int wn = wave * 16;
+  double ns = kFixed + t * ((KT + p.splits - 1) / p.splits);
+  if (p.splits > 1) ns += kSplitValue * static_cast<double>(M) * n * p.splits;
+  const double stream = kFixed + 2.0 * n * static_cast<double>(k) / kStream;
+  return ns > stream ? ns : stream;
+}
 
-  u32x4 rx[kSPer];
-  auto load_x = [&](int kt) {
-#pragma unroll
-    for (int i = 0; i < kSPer; ++i) {
-      const int u = tid + i * kSThreads;
-      const int64_t gr = m0 + u / kGUnits;
-      const int kk = kt * kGK + (u % kGUnits) * 8;
-      rx[i] = gr < M ? *reinterpret_cast<const u32x4*>(x + gr * k + kk) : u32x4{0, 0, 0, 0};
-    }
-  };
-  auto store_x = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < kSPer; ++i) {
-      const int u = tid + i * kSThreads;
-      *reinterpret_cast<u32x4*>(&sm.x[buf][u / kGUnits][(u % kGUnits) * 8]) = rx[i];
-    }
-  };
-  // rows past n read row n - 1 (finite values whose sums are never stored).
-  // The W fragments of the current and of the next k tile are separate named
-  // registers (a runtime-indexed pair would become selects that wait for the
-  // load just issued).
-  const uint16_t* wrow = w + static_cast<int64_t>(min(n0 + wn + c16, n - 1)) * k + q4 * 8;
-  auto load_w = [&](int kt, bf16x8 (&f)[2]) {
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-      f[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(wrow + kt * kGK + ks * 32));
-  };
-  bf16x8 wcur[2], wnext[2];
-
-  f32x4 acc[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  if (kt0 < kt1) {
-    load_x(kt0);
-    load_w(kt0, wcur);
-    store_x(0);
-  }
-  __syncthreads();
-  if (kt0 + 1 < kt1) {
-    load_x(kt0 + 1);
-    load_w(kt0 + 1, wnext);
-  }
-  for (int kt = kt0; kt < kt1; ++kt) {
-    const int cur = (kt - kt0) & 1;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bf16x8 fx = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const u32x4*>(&sm.x[cur][i * 16 + c16][ks * 32 + q4 * 8]));
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wcur[ks], fx, acc[i], 0, 0, 0);
+// The best part for M rows with at most `bytes` of workspace.
+GemmPart gemm_best_part(int64_t M, int n, int k, int64_t bytes, double* ns) {
+  GemmPart best;
+  *ns = 1e300;
+  for (int cfg = 0; cfg < 3; ++cfg)
+    for (int s = 1; s <= kGMaxSplits && (s == 1 || 2 * s <= k / kGK); s *= 2) {
+      if (s > 1 && static_cast<double>(s) * M * n * 4 > static_cast<double>(bytes)) break;
+      GemmPart p;
+      p.cfg = cfg;
+      p.splits = s;
+      const double t = gemm_estimate(p, M, n, k);
+      if (t < *ns) {
+        *ns = t;
+        best = p;
       }
     }
-    if (kt + 1 < kt1) {
-      store_x(cur ^ 1);
-      wcur[0] = wnext[0];
-      wcur[1] = wnext[1];
-      if (kt + 2 < kt1) {
-        load_x(kt + 2);
-        load_w(kt + 2, wnext);
-      }
+  return best;
+}
+
+// All M rows in one part, or the whole 256-row tiles on the largest tile and
+// the remaining rows in a part of their own (a partial large tile costs as much
+// as a full one, and often a whole round of the chip).
+struct GemmPlan {
+  int64_t m_main = 0;  // rows of `main`; the other rows go to `tail`
+  GemmPart main, tail;
+};
+
+GemmPlan gemm_plan(int64_t M, int n, int k, int64_t bytes) {
+  GemmPlan plan;
+  double whole;
+  plan.main = gemm_best_part(M, n, k, bytes, &whole);
+  plan.m_main = M;
+  const int64_t rows = M / kBM * kBM;
+  if (rows > 0 && rows < M) {
+    double a, b;
+    const GemmPart body = gemm_best_part(rows, n, k, bytes, &a);
+    const GemmPart tail = gemm_best_part(M - rows, n, k, bytes, &b);
+    if (body.cfg == 0 && a + b < whole) {
+      plan.m_main = rows;
+      plan.main = body;
+      plan.tail = tail;
     }
-    __syncthreads();
   }
-  // lane holds rows i*16 + c16, columns q4*4 .. q4*4+3 of its wave's 16
-  float* ps = part + static_cast<int64_t>(s) * M * n;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t gr = m0 + i * 16 + c16;
-    if (gr >= M) continue;
-    const int gc = n0 + wn + q4 * 4;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (gc + r < n) ps[gr * n + gc + r] = acc[i][r];
+  return plan;
+}
+
+int64_t gemm_plan_bytes(const GemmPlan& p, int64_t M, int n) {
+  auto part = [&](const GemmPart& g, int64_t m) { return g.splits > 1 ? g.splits * m * n * 4 : 0; };
+  return max(part(p.main, p.m_main), part(p.tail, M - p.m_main));
+}
+
+template <typename C>
+int launch_tiles(int splits, int64_t M, int n, int k, const uint16_t* x, const uint16_t* w,
+                 const uint16_t* res, uint16_t* y, float* part, hipStream_t stream) {
+  const int64_t tm = (M + C::BM - 1) / C::BM;
+  const int tn = (n + C::BN - 1) / C::BN;
+  if (tm * tn > 0x7fffffff) return fail(RC_ERR_UNSUPPORTED, "grid too large");
+  const int vec = n % 4 == 0 && reinterpret_cast<uintptr_t>(y) % 8 == 0 &&
+                  reinterpret_cast<uintptr_t>(res) % 8 == 0;
+  const dim3 grid(static_cast<unsigned>(tm * tn), static_cast<unsigned>(splits));
+  if (splits == 1) {
+    hipLaunchKernelGGL((gemm_bf16_tile_kernel<C, false>), grid, dim3(C::Threads), 0, stream, x, w, res,
+                       y, part, M, n, k, static_cast<int>(tm), tn, vec);
+    return check_launch("rc_gemm_bf16");
+  }
+  hipLaunchKernelGGL((gemm_bf16_tile_kernel<C, true>), grid, dim3(C::Threads), 0, stream, x, w, res, y,
+                     part, M, n, k, static_cast<int>(tm), tn, n % 4 == 0 ? 1 : 0);
+  if (int st = check_launch("rc_gemm_bf16")) return st;
+  const int64_t count = M * n;
+  hipLaunchKernelGGL(gemm_reduce_kernel, dim3(static_cast<unsigned>((count + 1023) / 1024)), dim3(256), 0,
+                     stream, part, res, y, count, splits, vec);
+  return check_launch("rc_gemm_bf16");
+}
+
+int launch_part(const GemmPart& p, int64_t M, int n, int k, const uint16_t* x, const uint16_t* w,
+                const uint16_t* res, uint16_t* y, float* part, hipStream_t stream) {
+  switch (p.cfg) {
+    case 0: return launch_tiles<CfgBig>(p.splits, M, n, k, x, w, res, y, part, stream);
+    case 1: return launch_tiles<CfgMid>(p.splits, M, n, k, x, w, res, y, part, stream);
+    default: return launch_tiles<CfgSmall>(p.splits, M, n, k, x, w, res, y, part, stream);
   }
 }
 
-// y[m, c] = bf16(sum over s of part[s][m, c] (+ residual[m, c])), s in order
-__global__ __launch_bounds__(256)
-void gemm_tail_reduce_kernel(const float* __restrict__ part, const uint16_t* __restrict__ res,
-                             uint16_t* __restrict__ y, int64_t count, int splits) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= count) return;
-  float v = part[e];
-  for (int s = 1; s < splits; ++s) v += part[static_cast<int64_t>(s) * count + e];
-  if (res) v += bf16_to_f32(res[e]);
-  y[e] = f32_to_bf16(v);
+bool gemm_tiles_ok(int k, const void* x, const void* w) {
+  return k % kGK == 0 && k <= kGMaxK && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
+         reinterpret_cast<uintptr_t>(w) % 16 == 0;
+}
+
+int gemm_impl(int64_t M, int32_t n, int32_t k, const void* x, const void* w, const void* residual,
+              void* y, void* workspace, int64_t workspace_bytes, hipStream_t stream) {
+  if (!x || !w || !y) return fail(RC_ERR_INVALID_ARG, "x, w and y must be non-NULL");
+  if (M < 0 || n < 1 || k < 8 || k % 8)
+    return fail(RC_ERR_INVALID_ARG, "M=%lld n=%d k=%d (k a positive multiple of 8)",
+                static_cast<long long>(M), n, k);
+  if (workspace_bytes < 0) return fail(RC_ERR_INVALID_ARG, "workspace_bytes must be >= 0");
+  if (M == 0) return RC_OK;
+  auto overlaps = [](const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    return a0 < b0 + static_cast<uintptr_t>(b_bytes) && b0 < a0 + static_cast<uintptr_t>(a_bytes);
+  };
+  const int64_t x_bytes = M * k * 2, w_bytes = static_cast<int64_t>(n) * k * 2, y_bytes = M * n * 2;
+  if (overlaps(y, y_bytes, x, x_bytes) || overlaps(y, y_bytes, w, w_bytes) ||
+      (residual && overlaps(y, y_bytes, residual, y_bytes)))
+    return fail(RC_ERR_INVALID_ARG, "y must not alias or overlap x, w or residual");
+  if (workspace && (overlaps(workspace, workspace_bytes, x, x_bytes) ||
+                    overlaps(workspace, workspace_bytes, w, w_bytes) ||
+                    overlaps(workspace, workspace_bytes, y, y_bytes) ||
+                    (residual && overlaps(workspace, workspace_bytes, residual, y_bytes))))
+    return fail(RC_ERR_INVALID_ARG, "workspace must not overlap x, w, y or residual");
+  const uint16_t* xs = static_cast<const uint16_t*>(x);
+  const uint16_t* ws = static_cast<const uint16_t*>(w);
+  const uint16_t* rs = static_cast<const uint16_t*>(residual);
+  uint16_t* ys = static_cast<uint16_t*>(y);
+  if (!gemm_tiles_ok(k, x, w)) {
+    const int vec = n % 4 == 0 && reinterpret_cast<uintptr_t>(y) % 8 == 0 &&
+                    reinterpret_cast<uintptr_t>(residual) % 8 == 0;
+    const int64_t tiles_m = (M + kGM - 1) / kGM;
+    const int tiles_n = (n + kGN - 1) / kGN;
+    const int64_t blocks = tiles_m * tiles_n;
+    if (blocks > 0x7fffffff) return fail(RC_ERR_UNSUPPORTED, "grid too large");
+    hipLaunchKernelGGL(gemm_bf16_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kGThreads), 0, stream,
+                       xs, ws, rs, ys, M, n, k, static_cast<int>(tiles_m), tiles_n, vec);
+    return check_launch("rc_gemm_bf16");
+  }
+  float* part = static_cast<float*>(workspace);
+  const bool have = workspace && reinterpret_cast<uintptr_t>(workspace) % 16 == 0;
+  GemmPlan plan = gemm_plan(M, n, k, have ? min(workspace_bytes, kGMaxWorkspace) : 0);
+  if (!have && M >= kBM && n >= kBN && M % kBM != 0) {
+    // without a workspace: the whole 256-row tiles on the largest tile; the
+    // remaining rows split over k, when the middle tile would run them on few
+    // workgroups, with their partial sums in the first rows of y, which the
+    // large tiles overwrite afterwards on the same stream (about 512
+    // workgroups, at least 2 k tiles each)
+    const int64_t M_main = M / kBM * kBM;
+    const int64_t M_tail = M - M_main;
+    const int64_t small_tiles = ((M_tail + kGM - 1) / kGM) * ((n + kGN - 1) / kGN);
+    const int64_t split_tiles = ((M_tail + kSM - 1) / kSM) * ((n + kSN - 1) / kSN);
+    int64_t splits = min(512 / split_tiles, static_cast<int64_t>(k / kGK / 2));
+    splits = min(splits, M_main / (2 * M_tail));
+    plan = GemmPlan{};
+    plan.m_main = M_main;
+    plan.tail.cfg = 1;
+    if (small_tiles < 128 && splits >= 2 && reinterpret_cast<uintptr_t>(y) % 16 == 0) {
+      plan.tail.cfg = 2;
+      plan.tail.splits = static_cast<int>(splits);
+      part = reinterpret_cast<float*>(ys);
+    }
+  }
+  const int64_t mm = plan.m_main;
+  if (mm < M) {
+    if (int st = launch_part(plan.tail, M - mm, n, k, xs + mm * k, ws, rs ? rs + mm * n : nullptr,
+                             ys + mm * n, part, stream))
+      return st;
+  }
+  return launch_part(plan.main, mm, n, k, xs, ws, rs, ys, part, stream);
 }
 
 }  // namespace
@@ -419,79 +673,18 @@ void gemm_tail_reduce_kernel(const float* __restrict__ part, const uint16_t* __r
 
 extern "C" int rc_gemm_bf16(int64_t M, int32_t n, int32_t k, const void* x, const void* w,
                             const void* residual, void* y, hipStream_t stream) {
-  using namespace rc;
-  clear_error();
-  if (!x || !w || !y) return fail(RC_ERR_INVALID_ARG, "x, w and y must be non-NULL");
-  if (M < 0 || n < 1 || k < 8 || k % 8)
-    return fail(RC_ERR_INVALID_ARG, "M=%lld n=%d k=%d (k a positive multiple of 8)",
-                static_cast<long long>(M), n, k);
-  if (M == 0) return RC_OK;
-  auto overlaps = [](const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
-    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
-    return a0 < b0 + static_cast<uintptr_t>(b_bytes) && b0 < a0 + static_cast<uintptr_t>(a_bytes);
-  };
-  const int64_t y_bytes = M * n * 2;
-  if (overlaps(y, y_bytes, x, M * k * 2) || overlaps(y, y_bytes, w, static_cast<int64_t>(n) * k * 2) ||
-      (residual && overlaps(y, y_bytes, residual, y_bytes)))
-    return fail(RC_ERR_INVALID_ARG, "y must not alias or overlap x, w or residual");
-  const uint16_t* xs = static_cast<const uint16_t*>(x);
-  const uint16_t* rs = static_cast<const uint16_t*>(residual);
-  uint16_t* ys = static_cast<uint16_t*>(y);
-  const int vec = n % 4 == 0 && reinterpret_cast<uintptr_t>(y) % 8 == 0 &&
-                  reinterpret_cast<uintptr_t>(residual) % 8 == 0;
-  if (k % kGK == 0 && M >= kBM && n >= kBN) {
-    // whole 256-row tiles on the big kernel; a tail of fewer than 256 rows
-    // goes to split-K (below) when the 128 x 128 kernel would run it on few
-    // workgroups, else to that kernel (a partial big tile would cost as much
-    // as a full one and, with few tiles per CU, a whole extra round)
-    const int64_t M_main = (M / kBM) * kBM;
-    const int64_t tm = M_main / kBM;
-    const int tn = (n + kBN - 1) / kBN;
-    if (tm * tn > 0x7fffffff) return fail(RC_ERR_UNSUPPORTED, "grid too large");
-    const int64_t M_tail = M - M_main;
-    const int KT = k / kGK;
-    const int64_t small_tiles = ((M_tail + kGM - 1) / kGM) * ((n + kGN - 1) / kGN);
-    const int64_t split_tiles = ((M_tail + kSM - 1) / kSM) * ((n + kSN - 1) / kSN);
-    // splits: about 512 workgroups, at least 2 k tiles each, and the partials
-    // (splits x M_tail x n fp32) inside the first M_main rows of y (bf16)
-    int64_t splits64 = 512 / (split_tiles > 0 ? split_tiles : 1);
-    if (splits64 > KT / 2) splits64 = KT / 2;
-    if (M_tail > 0 && splits64 > M_main / (2 * M_tail)) splits64 = M_main / (2 * M_tail);
-    const int splits = static_cast<int>(splits64);
-    if (M_tail > 0 && small_tiles < 128 && splits >= 2 && reinterpret_cast<uintptr_t>(y) % 16 == 0) {
-      float* part = reinterpret_cast<float*>(ys);
-      hipLaunchKernelGGL(gemm_bf16_splitk_kernel,
-                         dim3(static_cast<unsigned>((n + kSN - 1) / kSN), static_cast<unsigned>((M_tail + kSM - 1) / kSM),
-                              static_cast<unsigned>(splits)),
-                         dim3(kSThreads), 0, stream, xs + M_main * k, static_cast<const uint16_t*>(w), part,
-                         M_tail, n, k, splits);
-      if (int st = check_launch("rc_gemm_bf16")) return st;
-      const int64_t count = M_tail * n;
-      hipLaunchKernelGGL(gemm_tail_reduce_kernel, dim3(static_cast<unsigned>((count + 255) / 256)), dim3(256), 0,
-                         stream, part, rs ? rs + M_main * n : nullptr, ys + M_main * n, count, splits);
-      if (int st = check_launch("rc_gemm_bf16")) return st;
-      // the body last: it overwrites the partials
-      hipLaunchKernelGGL(gemm_bf16_big_kernel, dim3(static_cast<unsigned>(tm * tn)), dim3(kBThreads), 0,
-                         stream, xs, static_cast<const uint16_t*>(w), rs, ys, M_main, n, k,
-                         static_cast<int>(tm), tn, vec);
-      return check_launch("rc_gemm_bf16");
-    }
-    hipLaunchKernelGGL(gemm_bf16_big_kernel, dim3(static_cast<unsigned>(tm * tn)), dim3(kBThreads), 0,
-                       stream, xs, static_cast<const uint16_t*>(w), rs, ys, M_main, n, k,
-                       static_cast<int>(tm), tn, vec);
-    if (int st = check_launch("rc_gemm_bf16")) return st;
-    if (M_main == M) return RC_OK;
-    xs += M_main * k;
-    if (rs) rs += M_main * n;
-    ys += M_main * n;
-    M -= M_main;
-  }
-  const int64_t tiles_m = (M + kGM - 1) / kGM;
-  const int tiles_n = (n + kGN - 1) / kGN;
-  const int64_t blocks = tiles_m * tiles_n;
-  if (blocks > 0x7fffffff) return fail(RC_ERR_UNSUPPORTED, "grid too large");
-  hipLaunchKernelGGL(gemm_bf16_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kGThreads), 0,
-                     stream, xs, static_cast<const uint16_t*>(w), rs, ys, M, n, k,
-                     static_cast<int>(tiles_m), tiles_n, vec);
-  return check_launch("rc_gemm_bf16");
+  rc::clear_error();
+  return rc::gemm_impl(M, n, k, x, w, residual, y, nullptr, 0, stream);
+}
+
+extern "C" int64_t rc_gemm_workspace_bytes(int64_t M, int32_t n, int32_t k) {
+  if (M < 1 || n < 1 || k < 8 || k % rc::kGK != 0 || k > rc::kGMaxK) return 0;
+  return rc::gemm_plan_bytes(rc::gemm_plan(M, n, k, rc::kGMaxWorkspace), M, n);
+}
+
+extern "C" int rc_gemm_bf16_ws(int64_t M, int32_t n, int32_t k, const void* x, const void* w,
+                               const void* residual, void* y, void* workspace,
+                               int64_t workspace_bytes, hipStream_t stream) {
+  rc::clear_error();
+  return rc::gemm_impl(M, n, k, x, w, residual, y, workspace, workspace_bytes, stream);
 }

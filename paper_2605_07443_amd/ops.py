@@ -622,16 +622,31 @@ def full_prefill(q, k_fresh, v_fresh, scale=None, out=None, stream=None):
 
 # ------------------------------------------------------- several layers
 
+def _workspace(nbytes: int, device, stream=None):
+    """Scratch memory of one call, from torch's allocator on the stream that
+    runs the call (so that it is reused only after it)."""
+    if nbytes == 0:
+        return None
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
 def gemm(x, w, residual=None, out=None, stream=None):
-    """rc_gemm_bf16: out[M, n] = x[M, k] @ w[n, k]^T (+ residual)."""
+    """rc_gemm_bf16_ws: out[M, n] = x[M, k] @ w[n, k]^T (+ residual)."""
     M, k = x.shape
     n = w.shape[0]
     if w.shape[1] != k:
         raise ValueError(f"x [M, {k}] and w [{n}, {w.shape[1]}] do not match")
     out = torch.empty((M, n), dtype=x.dtype, device=x.device) if out is None else out
-    check(_lib.load().rc_gemm_bf16(
+    lib = _lib.load()
+    nbytes = lib.rc_gemm_workspace_bytes(M, n, k)
+    ws = _workspace(nbytes, x.device, stream)
+    check(lib.rc_gemm_bf16_ws(
         int(M), int(n), int(k), _dev(x, "x"), _dev(w, "w"),
-        None if residual is None else _dev(residual, "residual"), _dev(out, "out"), _stream(stream)))
+        None if residual is None else _dev(residual, "residual"), _dev(out, "out"),
+        None if ws is None else ws.data_ptr(), nbytes, _stream(stream)))
     return out
 
 

@@ -1,0 +1,99 @@
+"""rc_gemm_bf16 / rc_gemm_bf16_ws: every tile shape, split count and row tail
+that the plan can choose, at the edges of the tiles."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_07443_amd import _lib, ops
+
+DEV = "cuda:0"
+
+
+def test_workspace_bytes_are_bounded():
+    """Host rule: 0 where the tiled kernel does not run or no split pays off,
+    else whole fp32 partial sums of some rows, at most 128 MiB."""
+    lib = _lib.load()
+    assert lib.rc_gemm_workspace_bytes(0, 64, 64) == 0
+    assert lib.rc_gemm_workspace_bytes(48, 4096, 72) == 0
+    assert lib.rc_gemm_workspace_bytes(4096, 4096, 4096) == 0       # a whole round of large tiles
+    for M, n, k in [(1, 8, 4096), (48, 4096, 4096), (506, 4096, 14336), (4160, 4096, 14336),
+                    (100000, 28672, 4096), (2024, 4096, 1 << 20)]:
+        b = lib.rc_gemm_workspace_bytes(M, n, k)
+        assert 0 <= b <= 128 << 20 and b % (4 * n) == 0, (M, n, k, b)
+    assert lib.rc_gemm_workspace_bytes(48, 4096, 14336) > 0
+
+
+# rounding of the result to bf16 is 2^-9 relative, the fp32 sums of up to 7168
+# products of size 1/sqrt(k) add less than 1e-4
+RTOL, ATOL = 8e-3, 2e-3
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,n,k,res", [
+    (1, 8, 64, False), (1, 4096, 4096, True), (48, 4096, 4096, False), (63, 129, 128, True),
+    (64, 128, 2048, True), (65, 127, 1984, False), (127, 260, 7168, True), (129, 640, 64, False),
+    (255, 256, 192, True), (256, 255, 64, False), (257, 513, 4096, True), (312, 1024, 4096, True),
+    (506, 1026, 7168, False), (1012, 2048, 2048, True), (2049, 512, 640, False),
+    (4160, 1024, 512, True)])
+def test_gemm_with_and_without_workspace(M, n, k, res):
+    print(f"[gemm ws] M={M} n={n} k={k} bytes={_lib.load().rc_gemm_workspace_bytes(M, n, k)}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(M * 31 + n)
+    x = torch.randn((M, k), generator=g, device=DEV).to(torch.bfloat16)
+    w = (torch.randn((n, k), generator=g, device=DEV) / k ** 0.5).to(torch.bfloat16)
+    r = torch.randn((M, n), generator=g, device=DEV).to(torch.bfloat16) if res else None
+    want = (x.double() @ w.double().t() + (0 if r is None else r.double())).cpu().numpy()
+    y = ops.gemm(x, w, r)
+    again = ops.gemm(x, w, r)
+    plain = torch.full_like(y, 7.0)
+    vp = ctypes.c_void_p
+    _lib.check(_lib.load().rc_gemm_bf16(M, n, k, vp(x.data_ptr()), vp(w.data_ptr()),
+                                        None if r is None else vp(r.data_ptr()), vp(plain.data_ptr()),
+                                        vp(torch.cuda.current_stream().cuda_stream)))
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(torch.int16), again.view(torch.int16))
+    for got in (y, plain):
+        np.testing.assert_allclose(got.double().cpu().numpy(), want, rtol=RTOL, atol=ATOL)
+
+
+@pytest.mark.gpu
+def test_gemm_operands_off_a_16_byte_boundary():
+    """x and w start 2 bytes into their buffers: the register-staged kernel."""
+    M, n, k = 70, 96, 128
+    g = torch.Generator(device=DEV).manual_seed(3)
+    xb = torch.randn(M * k + 1, generator=g, device=DEV).to(torch.bfloat16)
+    wb = (torch.randn(n * k + 1, generator=g, device=DEV) / k ** 0.5).to(torch.bfloat16)
+    x, w = xb[1:].view(M, k), wb[1:].view(n, k)
+    y = ops.gemm(x, w)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(y.double().cpu().numpy(), (x.double() @ w.double().t()).cpu().numpy(),
+                               rtol=RTOL, atol=ATOL)
+
+
+@pytest.mark.gpu
+def test_gemm_split_on_a_side_stream_and_captured():
+    """The workspace belongs to the stream that runs the call; a captured call
+    replays to the eager result."""
+    M, n, k = 48, 1024, 4096
+    g = torch.Generator(device=DEV).manual_seed(4)
+    x = torch.randn((M, k), generator=g, device=DEV).to(torch.bfloat16)
+    w = (torch.randn((n, k), generator=g, device=DEV) / k ** 0.5).to(torch.bfloat16)
+    assert _lib.load().rc_gemm_workspace_bytes(M, n, k) > 0
+    want = ops.gemm(x, w)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    y = ops.gemm(x, w, out=torch.empty_like(want), stream=side)
+    side.synchronize()
+    assert torch.equal(y, want)
+    out = torch.empty_like(want)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ops.gemm(x, w, out=out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        ops.gemm(x, w)
