@@ -40,7 +40,7 @@
 // update of Sec. III-C.3 (iii)), or the pool row, whose key pairs are rotated
 // by the segment's dst_start in registers (step (ii)) before they reach LDS.
 // The tiles are then bit-identical to those of the assembled path.
-// fp32 path: one wave per (request, row, head), fp32 FMA on the vector ALUs.
+// fp32 path: attn_f32_kernel below.
 #include <cmath>
 #include <type_traits>
 
@@ -806,72 +806,220 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
   }
 }
 
-// fp32: one wave per (request, row, q-head). Lanes own keys while scoring
-// (64 keys per step) and dims while accumulating P V.
+// fp32 path: products on the matrix cores (v_mfma_f32_16x16x4_f32, fp32 in and
+// out), everything from global memory straight into registers.
+//   * A workgroup owns 16 query vectors (16 consecutive (row, head) pairs of one
+//     request and KV head; any group size). Its 8 waves take the chunks of
+//     16 KB keys in turn and each keeps its own online softmax; the partial
+//     (max, sum, O) of the waves are merged through LDS at the end, in a fixed
+//     order. Few vectors per workgroup and the split over keys are what the
+//     small fp32 shapes need: 90 rows x 8 heads over 416 keys are 48 workgroups
+//     of one chunk per wave, a chain of two memory round trips.
+//   * S^T = K Q^T: the sum over d is taken in the order that makes every load a
+//     16-byte one: lane (q4, c16) holds elements q4 D/4 .. + D/4 - 1 of key (or
+//     query) c16, and step s multiplies element s of each quarter.
+//   * O^T = V^T P^T: a lane's scores are keys 4 q4 + i of query c16, so step i
+//     multiplies P in place with V row 4 q4 + i; output row r of block db is
+//     dim r D/16 + db, so that a lane's V elements are contiguous too.
+// Measured against one wave per row and head (dwords of 64 different key rows
+// per load): every row of 416 x 8 heads of 64 69 -> 14 us (latency: launch, two
+// memory round trips, the merge), of 2,000 x 32 / 8 heads of 128 5.26 ms ->
+// 0.65 ms (50 TFLOP/s of the 150 the fp32 products reach in a large GEMM; K and
+// V come from L2 once per 16 vectors).
+// Keys past a query get weight 0 in the products of a chunk that other queries
+// still see; should such a chunk hold an infinity or NaN in V (0 times it is not
+// 0), its products are formed on the vector ALU for the seen keys alone.
+constexpr int kF32Waves = 8;
+constexpr int kF32Threads = kF32Waves * 64;
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));  // tensors need only fp32 alignment
+
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ q,
-                                                       const int32_t* __restrict__ rows, int R,
-                                                       int N, int Hq, int Hkv,
-                                                       const float* __restrict__ k,
-                                                       const float* __restrict__ v, float scale,
-                                                       float* __restrict__ out,
-                                                       float* __restrict__ lse, int64_t total) {
-  constexpr int PER = D / 64;
-  __shared__ float s_q[4][D];
+__global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(
+    const float* __restrict__ q, const int32_t* __restrict__ rows, int R, int N, int Hq, int Hkv,
+    const float* __restrict__ k, const float* __restrict__ v, float scale, float* __restrict__ out,
+    float* __restrict__ lse, int n_tiles, int n_groups) {
+  constexpr int E = D / 4;            // d elements per lane of a K or Q row
+  constexpr int DB = D / 16;          // 16-row blocks of O^T; V elements per lane and key
+  constexpr int KB = D == 64 ? 4 : 2; // 16-key blocks per chunk
+  constexpr int KC = KB * 16;
+  __shared__ float s_m[kF32Waves / 2][16], s_l[kF32Waves / 2][16];
+  __shared__ f32x4 s_o[kF32Waves / 2][DB][64];
+  const int grp = blockIdx.x % n_groups;
+  const int tile = n_tiles - 1 - blockIdx.x / n_groups;   // longest rows first
+  const int b = grp / Hkv;
+  const int g = grp - b * Hkv;
+  const int G = Hq / Hkv;
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int64_t w = static_cast<int64_t>(blockIdx.x) * 4 + wave;
-  const bool active = w < total;
-  const int64_t wi = active ? w : 0;
-  const int h = static_cast<int>(wi % Hq);
-  const int64_t br = wi / Hq;
-  const int r = static_cast<int>(br % R);
-  const int b = static_cast<int>(br / R);
-  int p = rows ? rows[static_cast<size_t>(b) * R + r] : r;
-  const bool bad = p < 0 || p >= N;   // computes row 0, stores NaN
-  p = bad ? 0 : p;
-  const int g = h / (Hq / Hkv);
-  const float* qrow = q + ((static_cast<size_t>(b) * N + p) * Hq + h) * D;
-  for (int d = lane; d < D; d += 64) s_q[wave][d] = qrow[d];
-  __syncthreads();
-  if (!active) return;
-  const size_t kv_stride = static_cast<size_t>(Hkv) * D;
-  const float* kb = k + static_cast<size_t>(b) * N * kv_stride + static_cast<size_t>(g) * D;
-  const float* vb = v + static_cast<size_t>(b) * N * kv_stride + static_cast<size_t>(g) * D;
-  float m = -INFINITY, l = 0.f, acc[PER];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15;
+  const int q4 = lane >> 4;
+
+  // ---- this lane's query vector
+  const int64_t vec = static_cast<int64_t>(tile) * 16 + c16;
+  const bool valid = vec < static_cast<int64_t>(R) * G;
+  const int row = valid ? static_cast<int>(vec / G) : 0;
+  const int head = g * G + (valid ? static_cast<int>(vec % G) : 0);
+  int pos = 0;
+  if (valid) pos = rows ? rows[static_cast<size_t>(b) * R + row] : row;
+  const bool bad = pos < 0 || pos >= N;   // computes row 0, stores NaN
+  if (bad) pos = 0;
+  const int pmax = wave_max_i(pos);
+  const int pmin = wave_min_i(valid ? pos : 0x7fffffff);
+
+  float qf[E];
+  {
+    const f32x4_a4* qr = reinterpret_cast<const f32x4_a4*>(
+        q + ((static_cast<size_t>(b) * N + pos) * Hq + head) * D + q4 * E);
 #pragma unroll
-  for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-  for (int c = 0; c <= p; c += 64) {
-    const int j = c + lane;
-    float sc = -INFINITY;
-    if (j <= p) {
-      const float* kr = kb + j * kv_stride;
-      float dot = 0.f;
-#pragma unroll 8
-      for (int d = 0; d < D; ++d) dot = fmaf(s_q[wave][d], kr[d], dot);
-      sc = dot * scale;
+    for (int e = 0; e < E / 4; ++e) {
+      const f32x4 t = qr[e];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) qf[4 * e + i] = t[i];
     }
-    const float cm = wave_max(sc);
-    const float m_new = fmaxf(m, cm);
-    const float alpha = expf(m - m_new);
-    const float pj = j <= p ? expf(sc - m_new) : 0.f;
-    l = l * alpha + wave_sum(pj);
-#pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] *= alpha;
-    const int cnt = min(64, p - c + 1);
-    for (int jj = 0; jj < cnt; ++jj) {
-      const float pw = __shfl(pj, jj, 64);
-      const float* vr = vb + (c + jj) * kv_stride;
-#pragma unroll
-      for (int e = 0; e < PER; ++e) acc[e] = fmaf(pw, vr[lane * PER + e], acc[e]);
-    }
-    m = m_new;
   }
-  float* orow = out + ((static_cast<size_t>(b) * R + r) * Hq + h) * D;
-  const float nan = __builtin_nanf("");
+  const size_t stride = static_cast<size_t>(Hkv) * D;
+  const float* kb0 = k + static_cast<size_t>(b) * N * stride + static_cast<size_t>(g) * D;
+  const float* vb0 = v + static_cast<size_t>(b) * N * stride + static_cast<size_t>(g) * D;
+
+  f32x4 o[DB];
 #pragma unroll
-  for (int e = 0; e < PER; ++e) orow[lane * PER + e] = bad ? nan : acc[e] / l;
-  if (lse && lane == 0) lse[(static_cast<size_t>(b) * R + r) * Hq + h] = bad ? nan : m + logf(l);
+  for (int db = 0; db < DB; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  const int n_chunks = pmax / KC + 1;
+  for (int c = wave; c < n_chunks; c += kF32Waves) {
+    const int j0 = c * KC;
+    // ---- loads of the chunk (keys past N repeat the last one; they are masked)
+    f32x4 kf[KB][E / 4], vf[KB][4][DB / 4];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const f32x4_a4* kr = reinterpret_cast<const f32x4_a4*>(
+          kb0 + static_cast<size_t>(min(j0 + kb * 16 + c16, N - 1)) * stride + q4 * E);
+#pragma unroll
+      for (int e = 0; e < E / 4; ++e) kf[kb][e] = kr[e];
+    }
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4_a4* vr = reinterpret_cast<const f32x4_a4*>(
+            vb0 + static_cast<size_t>(min(j0 + kb * 16 + q4 * 4 + i, N - 1)) * stride + c16 * DB);
+#pragma unroll
+        for (int e = 0; e < DB / 4; ++e) vf[kb][i][e] = vr[e];
+      }
+    // ---- scores
+    f32x4 s[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) s[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][e / 4][e % 4], qf[e], s[kb], 0, 0, 0);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s[kb][i] = j0 + kb * 16 + q4 * 4 + i <= pos ? s[kb][i] * scale : -INFINITY;
+        mx = fmaxf(mx, s[kb][i]);
+      }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m, mx);
+    const float ref = m_new == -INFINITY ? 0.f : m_new;   // no key seen yet: weights are 0
+    const float alpha = expf(m - ref);
+    l *= alpha;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] *= alpha;
+    m = m_new;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[kb][i] = expf(s[kb][i] - ref);
+      l += (s[kb][0] + s[kb][1]) + (s[kb][2] + s[kb][3]);
+    }
+    // ---- O^T += V^T P^T
+    if (j0 + KC - 1 > pmin) {
+      bool odd = false;   // an infinity or NaN among the chunk's values
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int e = 0; e < DB / 4; ++e)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) odd |= !(fabsf(vf[kb][i][e][x]) < INFINITY);
+      if (__ballot(odd) != 0) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            for (int qq = 0; qq < 4; ++qq) {
+              const float p = __shfl(s[kb][i], qq * 16 + c16, 64);
+              const int j = j0 + kb * 16 + qq * 4 + i;
+              if (j > pos) continue;
+              const float* vr = vb0 + static_cast<size_t>(j) * stride + 4 * q4 * DB;
+#pragma unroll
+              for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) o[db][x] = fmaf(p, vr[x * DB + db], o[db][x]);
+            }
+        continue;
+      }
+    }
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          o[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[kb][i][db / 4][db % 4], s[kb][i], o[db], 0, 0, 0);
+  }
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+
+  // ---- merge the waves: the upper half of them hands over, until one is left
+#pragma unroll
+  for (int half = kF32Waves / 2; half >= 1; half >>= 1) {
+    if (wave >= half && wave < 2 * half) {
+      if (q4 == 0) {
+        s_m[wave - half][c16] = m;
+        s_l[wave - half][c16] = l;
+      }
+#pragma unroll
+      for (int db = 0; db < DB; ++db) s_o[wave - half][db][lane] = o[db];
+    }
+    __syncthreads();
+    if (wave < half) {
+      const float mo = s_m[wave][c16], lo = s_l[wave][c16];
+      const float m_new = fmaxf(m, mo);
+      const float ref = m_new == -INFINITY ? 0.f : m_new;
+      const float fa = expf(m - ref), fb = expf(mo - ref);
+      l = l * fa + lo * fb;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const f32x4 t = s_o[wave][db][lane];
+        o[db] = o[db] * fa + t * fb;
+      }
+      m = m_new;
+    }
+    __syncthreads();
+  }
+  if (wave != 0 || !valid) return;
+  // lane: dims (4 q4 + i) DB + db of its query
+  const float nan = __builtin_nanf("");
+  f32x4_a4* orow = reinterpret_cast<f32x4_a4*>(out + ((static_cast<size_t>(b) * R + row) * Hq + head) * D);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int e = 0; e < DB / 4; ++e) {
+      f32x4 t;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) t[x] = bad ? nan : o[4 * e + x][i] / l;
+      orow[((4 * q4 + i) * DB) / 4 + e] = t;
+    }
+  if (lse && q4 == 0)
+    lse[(static_cast<size_t>(b) * R + row) * Hq + head] = bad ? nan : m + logf(l);
 }
 
 }  // namespace
@@ -950,20 +1098,17 @@ int attention_impl(const rc_shape* shape, const void* q, const int32_t* rows, in
     }
   } else {
     if (paged) return fail(RC_ERR_UNSUPPORTED, "paged attention is implemented for bf16");
-    const int64_t total = static_cast<int64_t>(B) * R * Hq;
-    const int64_t blocks = (total + 3) / 4;
+    const int64_t n_tiles = (static_cast<int64_t>(R) * G + 15) / 16;
+    const int n_groups = B * Hkv;
+    const int64_t blocks = n_tiles * n_groups;
     if (blocks > 0x7fffffff) return fail(RC_ERR_UNSUPPORTED, "grid too large");
-    dim3 grid(static_cast<unsigned>(blocks));
-    if (D == 128)
-      hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(256), 0, stream,
+    auto launch = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(blocks)), dim3(kF32Threads), 0, stream,
                          static_cast<const float*>(q), rows, R, N, Hq, Hkv,
                          static_cast<const float*>(k), static_cast<const float*>(v), scale,
-                         static_cast<float*>(out), lse, total);
-    else
-      hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, stream,
-                         static_cast<const float*>(q), rows, R, N, Hq, Hkv,
-                         static_cast<const float*>(k), static_cast<const float*>(v), scale,
-                         static_cast<float*>(out), lse, total);
+                         static_cast<float*>(out), lse, static_cast<int>(n_tiles), n_groups);
+    };
+    D == 128 ? launch(attn_f32_kernel<128>) : launch(attn_f32_kernel<64>);
   }
   return check_launch(what);
 }

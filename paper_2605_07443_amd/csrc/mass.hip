@@ -22,7 +22,7 @@
 //     atomics are needed and the result is deterministic.
 //   * Workgroups of one group run on one XCD (ids are dealt round-robin over
 //     the 8 XCDs), longest (earliest) key blocks first.
-// fp32 path: one thread per key, fp32 FMA on the vector ALUs.
+// fp32 path: mass_f32_kernel below.
 #include <cmath>
 #include <type_traits>
 
@@ -251,36 +251,96 @@ void mass_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
   }
 }
 
-// fp32: one thread per (request, group, key), rows p >= j of the group's heads.
+// fp32 path: S^T = K Q^T on the matrix cores (v_mfma_f32_16x16x4_f32, fp32 in
+// and out), operands from global memory straight into registers. A workgroup
+// owns 32 keys of one (request, KV group), held in registers by all of its 8
+// waves; the waves take the blocks of 16 query vectors (position-major, from
+// the first key's position on) in turn. Lane (q4, c16) holds elements
+// q4 D/4 .. + D/4 - 1 of key (or query vector) c16, and step s multiplies
+// element s of each quarter, so that every load is a 16-byte one. Each lane
+// sums the weights of its own keys and query columns; the columns are added by
+// shuffles and the waves through LDS in a fixed order. One thread per key (the
+// form before) left a 416-key request on 16 workgroups, each a chain of
+// 3,328 dot products: 231 -> 12 us for 416 positions of 8 heads of 64, 15.3 ->
+// 0.62 ms for 2,000 positions of 32 / 8 heads of 128.
+constexpr int kMassF32Waves = 8;
+constexpr int kMassF32Keys = 32;
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));  // tensors need only fp32 alignment
+
 template <int D>
-__global__ __launch_bounds__(256) void mass_f32_kernel(const float* __restrict__ q,
-                                                       const float* __restrict__ k,
-                                                       const float* __restrict__ lse, int N,
-                                                       int Hq, int Hkv, float scale,
-                                                       float* __restrict__ mass) {
+__global__ __launch_bounds__(kMassF32Waves * 64) void mass_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ lse, int N,
+    int Hq, int Hkv, float scale, float* __restrict__ mass) {
+  constexpr int E = D / 4;
+  constexpr int KB = kMassF32Keys / 16;
+  __shared__ float s_sum[kMassF32Waves][kMassF32Keys];
   const int G = Hq / Hkv;
   const int g = blockIdx.y % Hkv;
   const int b = blockIdx.y / Hkv;
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  const int jj = min(j, N - 1);
-  float kr[D];
-  const float* krow = k + ((static_cast<size_t>(b) * N + jj) * Hkv + g) * D;
+  const int j0 = blockIdx.x * kMassF32Keys;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15;
+  const int q4 = lane >> 4;
+  f32x4 kf[KB][E / 4];
 #pragma unroll
-  for (int d = 0; d < D; ++d) kr[d] = krow[d];
-  float acc = 0.f;
-  const int p_first = blockIdx.x * 256;  // uniform start; rows before j are masked
-  for (int p = p_first; p < N; ++p) {
-    for (int hh = 0; hh < G; ++hh) {
-      const int h = g * G + hh;
-      const float* qrow = q + ((static_cast<size_t>(b) * N + p) * Hq + h) * D;
-      float dot = 0.f;
+  for (int kb = 0; kb < KB; ++kb) {
+    const f32x4_a4* kr = reinterpret_cast<const f32x4_a4*>(
+        k + ((static_cast<size_t>(b) * N + min(j0 + kb * 16 + c16, N - 1)) * Hkv + g) * D + q4 * E);
 #pragma unroll
-      for (int d = 0; d < D; ++d) dot = fmaf(qrow[d], kr[d], dot);
-      const float w = expf(dot * scale - lse[(static_cast<size_t>(b) * N + p) * Hq + h]);
-      acc += (j <= p) ? w : 0.f;
-    }
+    for (int e = 0; e < E / 4; ++e) kf[kb][e] = kr[e];
   }
-  if (j < N) mass[(static_cast<size_t>(b) * Hkv + g) * N + j] = acc;
+  float acc[KB][4];
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[kb][i] = 0.f;
+  // query vectors of positions j0 .. N - 1: vector t is (position j0 + t / G, head t % G)
+  const int64_t n_vec = static_cast<int64_t>(N - j0) * G;
+  for (int64_t t0 = wave * 16; t0 < n_vec; t0 += kMassF32Waves * 16) {
+    const int64_t t = min(t0 + c16, n_vec - 1);
+    const int p = j0 + static_cast<int>(t / G);
+    const int h = g * G + static_cast<int>(t % G);
+    const f32x4_a4* qr = reinterpret_cast<const f32x4_a4*>(q + ((static_cast<size_t>(b) * N + p) * Hq + h) * D + q4 * E);
+    f32x4 qf[E / 4];
+#pragma unroll
+    for (int e = 0; e < E / 4; ++e) qf[e] = qr[e];
+    const float l = lse[(static_cast<size_t>(b) * N + p) * Hq + h];
+    f32x4 s[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) s[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][e / 4][e % 4], qf[e / 4][e % 4], s[kb], 0, 0, 0);
+    const int seen = t0 + c16 < n_vec ? p : -1;   // keys up to it; none for a vector past the end
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float w = expf(s[kb][i] * scale - l);
+        acc[kb][i] += j0 + kb * 16 + q4 * 4 + i <= seen ? w : 0.f;
+      }
+  }
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float x = acc[kb][i];
+      x += __shfl_xor(x, 1, 64);
+      x += __shfl_xor(x, 2, 64);
+      x += __shfl_xor(x, 4, 64);
+      x += __shfl_xor(x, 8, 64);
+      if (c16 == 0) s_sum[wave][kb * 16 + q4 * 4 + i] = x;
+    }
+  __syncthreads();
+  if (threadIdx.x < kMassF32Keys && j0 + threadIdx.x < N) {
+    float x = 0.f;
+#pragma unroll
+    for (int w = 0; w < kMassF32Waves; ++w) x += s_sum[w][threadIdx.x];
+    mass[(static_cast<size_t>(b) * Hkv + g) * N + j0 + threadIdx.x] = x;
+  }
 }
 
 }  // namespace
@@ -318,13 +378,13 @@ extern "C" int rc_attention_mass(const rc_shape* shape, const void* q, const voi
                          Hq, Hkv, G, g_shift, scale_log2e, mass, n_kblk, n_groups, gpx);
   } else {
     if (static_cast<int64_t>(B) * Hkv > 65535) return fail(RC_ERR_UNSUPPORTED, "B*Hkv exceeds 65535");
-    dim3 grid((N + 255) / 256, B * Hkv);
+    dim3 grid((N + kMassF32Keys - 1) / kMassF32Keys, B * Hkv);
     if (D == 128)
-      hipLaunchKernelGGL(mass_f32_kernel<128>, grid, dim3(256), 0, stream,
+      hipLaunchKernelGGL(mass_f32_kernel<128>, grid, dim3(kMassF32Waves * 64), 0, stream,
                          static_cast<const float*>(q), static_cast<const float*>(k), lse, N, Hq,
                          Hkv, scale, mass);
     else
-      hipLaunchKernelGGL(mass_f32_kernel<64>, grid, dim3(256), 0, stream,
+      hipLaunchKernelGGL(mass_f32_kernel<64>, grid, dim3(kMassF32Waves * 64), 0, stream,
                          static_cast<const float*>(q), static_cast<const float*>(k), lse, N, Hq,
                          Hkv, scale, mass);
   }
