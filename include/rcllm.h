@@ -317,6 +317,30 @@ int rc_selective_attention_vref(const rc_shape* shape, const void* q, const int3
                                 int32_t R, const void* k, const uint64_t* v_ref, float scale,
                                 void* out, hipStream_t stream);
 
+/* rc_selective_attention, rc_selective_attention_vref and rc_paged_attention
+ * with a workspace: a bf16 launch too small to occupy the GPU divides each
+ * row's keys over several workgroups, which leave fp32 partial outputs (and
+ * their maxima and sums) in the workspace; they are merged in a fixed order
+ * (deterministic; the three calls divide alike, so that they stay bit-identical
+ * to each other; outputs differ from an undivided call by rounding).
+ * workspace: device memory, 16-byte aligned, of
+ * rc_attention_workspace_bytes(shape, R) bytes (host function; 0 where the call
+ * is not divided, fp32 among it), used until `stream` has run the call. NULL or
+ * a smaller one: the call is not divided. Errors: those of the call without. */
+int64_t rc_attention_workspace_bytes(const rc_shape* shape, int32_t R);
+int rc_selective_attention_ws(const rc_shape* shape, const void* q, const int32_t* rows, int32_t R,
+                              const void* k, const void* v, float scale, void* out,
+                              void* workspace, int64_t workspace_bytes, hipStream_t stream);
+int rc_selective_attention_vref_ws(const rc_shape* shape, const void* q, const int32_t* rows,
+                                   int32_t R, const void* k, const uint64_t* v_ref, float scale,
+                                   void* out, void* workspace, int64_t workspace_bytes,
+                                   hipStream_t stream);
+int rc_paged_attention_ws(const rc_shape* shape, const void* q, const int32_t* rows, int32_t R,
+                          const rc_pool* pools, int32_t n_pools, const rc_segment* segs, int32_t S,
+                          const void* k_fresh, const void* v_fresh, const float* rope_cos,
+                          const float* rope_sin, int32_t max_pos, float scale, void* out,
+                          void* workspace, int64_t workspace_bytes, hipStream_t stream);
+
 /* Attention-mass term of Eq. (3) (Sec. III-C.2b: the first layer is computed
  * in full and a token's importance includes the attention weight it
  * receives). For KV group g and position j of request b:

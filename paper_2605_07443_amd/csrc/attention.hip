@@ -193,13 +193,22 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // in fp32 and bf16, and the O/l rescale is skipped on most tiles.
 constexpr float kLazy = 8.f;
 
+// A split that holds no key of a query reports this maximum (log2 units) and
+// sum 0, and its outputs are neither written nor read.
+constexpr float kNoKey = -1e30f;
+constexpr int kMaxSplits = 8;
+constexpr int kSplitTiles = 3;
+
 // SELECTIVE: query rows come from `rows`; otherwise row r is position r
 // (Full-Recompute). Separate instances keep the two modes apart in profiles.
 // LSE: also write each row's natural log-sum-exp, from an fp32 sum of the
 // unrounded exponentials (the bf16 column sums only normalise O).
 // PAGED: k, v are the fresh tensors; other keys come from `pools` through
 // `segs` (S <= kPagedMaxSegments), rotated with the cos/sin tables when given.
-template <int D, bool SELECTIVE, bool LSE, bool PAGED, bool VREF = false>
+// SPLIT: blockIdx.y is the split s of S; the workgroup takes the key tiles
+// [s n / S, (s + 1) n / S) of its n and leaves its running maximum, sum and
+// unnormalised outputs in `part` (attn_merge_kernel adds the splits in order).
+template <int D, bool SELECTIVE, bool LSE, bool PAGED, bool VREF = false, bool SPLIT = false>
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict__ rows, int R,
                       int N, int Hq, int Hkv, int G, int BR, int shift, const uint16_t* __restrict__ k,
@@ -207,7 +216,8 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
                       uint16_t* __restrict__ out, float* __restrict__ lse, int n_tiles,
                       int n_groups, int gpx, int chunk, PoolArgs pools,
                       const int4* __restrict__ segs, int S, const float* __restrict__ cos_t,
-                      const float* __restrict__ sin_t, int max_pos) {
+                      const float* __restrict__ sin_t, int max_pos, float* __restrict__ part) {
+  static_assert(!(SPLIT && LSE), "the log-sum-exp pass is not split");
   constexpr int DC = D / 32;          // 32-wide d chunks (S^T reduction)
   constexpr int DB = D / 16;          // 16-wide d blocks (O^T rows)
   constexpr int UPR = D / 8;          // 16-byte units per K/V head row
@@ -256,7 +266,7 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
     bad[nb] = false;
     int p = 0;
     if (valid[nb]) {
-      p = SELECTIVE ? rows[static_cast<size_t>(b) * R + r] : r;
+      p = SELECTIVE && (!SPLIT || rows != nullptr) ? rows[static_cast<size_t>(b) * R + r] : r;
       // a listed position outside [0, N) computes row 0 and stores NaN
       bad[nb] = p < 0 || p >= N;
       p = bad[nb] ? 0 : p;
@@ -281,7 +291,16 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
   }
   __syncthreads();
   const int wg_pmax = max(max(s_ext[0], s_ext[1]), max(s_ext[2], s_ext[3]));
-  const int n_kv = wg_pmax / kKT + 1;
+  // key tiles [t0, n_kv) of this workgroup; buffers alternate from t0 on
+  int t0 = 0, n_kv = wg_pmax / kKT + 1;
+  if constexpr (SPLIT) {
+    // rows that see few keys are divided into fewer, so that no split gets less
+    // than kSplitTiles tiles for its prologue and its part of the merge
+    const int n = n_kv, s = blockIdx.y;
+    const int parts = min(static_cast<int>(gridDim.y), max(1, n / kSplitTiles));
+    t0 = min(s, parts) * n / parts;
+    n_kv = min(s + 1, parts) * n / parts;
+  }
 
   // ---- Q fragments (B operand of S^T = K Q^T): 8 consecutive dims per lane
   bf16x8 qf[2][DC];
@@ -490,7 +509,10 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) o[db][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run[2] = {-INFINITY, -INFINITY};  // reference max of the unscaled scores
+  // reference max of the unscaled scores (a split may hold no key of a query:
+  // a finite start keeps that query's weights at 0)
+  constexpr float kStart = SPLIT ? -1e30f : -INFINITY;
+  float m_run[2] = {kStart, kStart};
   // softmax denominators on the matrix cores: ones(16x32) x P^T gives the
   // column sums of P for every query column (all 4 lanes' entries equal)
   f32x4 l_acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
@@ -531,17 +553,19 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
   using Buf0 = std::integral_constant<int, 0>;
   using Buf1 = std::integral_constant<int, 1>;
 
-  if constexpr (DIRECT) {
-    load_vent(0);   // tiles 0 and 1
+  if (SPLIT && t0 >= n_kv) {
+    // no tile for this split
+  } else if constexpr (DIRECT) {
+    load_vent(t0);   // the first two tiles
     spread_vent(Buf0{});
-    issue_tile(0, Buf0{});
+    issue_tile(t0, Buf0{});
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   } else {
-    load_tile(0);
+    load_tile(t0);
     store_tile(0);
     __syncthreads();
-    if (n_kv > 1) load_tile(1);
+    if (t0 + 1 < n_kv) load_tile(t0 + 1);
   }
 
   // first tile whose last key passes this wave's earliest row
@@ -742,14 +766,14 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
   // some row of this wave (a uniform branch).
   auto do_tile = [&](int t, auto buf_tag) {
     const bool MASK = t >= t_mask;                  // uniform: tiles past this wave's first row
-    constexpr int cur = decltype(buf_tag)::value;   // == t & 1
+    constexpr int cur = decltype(buf_tag)::value;   // == (t - t0) & 1
     using Next = std::integral_constant<int, cur ^ 1>;
     // DIRECT: the next tile flows into the other buffer during this one
     if constexpr (DIRECT) {
       if (t + 1 < n_kv) {
-        spread_vent(Next{});          // tile t + 1: half (t + 1) % 2 of the pair
+        spread_vent(Next{});          // tile t + 1: its half of the pair
         issue_tile(t + 1, Next{});
-        // even t: the pair (t + 2, t + 3), after its last use above
+        // first of a pair: the pair (t + 2, t + 3), after its last use above
         if (cur == 0 && t + 2 < n_kv) load_vent(t + 2);
       }
     }
@@ -770,7 +794,7 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
     __syncthreads();
   };
 
-  int t = 0;
+  int t = t0;
   for (; t + 1 < n_kv; t += 2) {
     do_tile(t, Buf0{});
     do_tile(t + 1, Buf1{});
@@ -790,6 +814,29 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
     }
   }
 
+  if constexpr (SPLIT) {
+    // per split, workgroup and wave w: the accumulators as they lie in the lanes
+    // [S][w][nb][db][lane] x 16 bytes, then (max in log2 units, sum) per query
+    // [S][w][nb][c16]; whole 1 KB stores
+    const size_t n_waves = static_cast<size_t>(n_groups) * n_tiles * 4;
+    const size_t w = (static_cast<size_t>(grp) * n_tiles + tile) * 4 + wave;
+    f32x4* po = reinterpret_cast<f32x4*>(part) + (blockIdx.y * n_waves + w) * (2 * DB * 64);
+    float2* pm = reinterpret_cast<float2*>(reinterpret_cast<f32x4*>(part) + gridDim.y * n_waves * (2 * DB * 64)) +
+                 (blockIdx.y * n_waves + w) * 32;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      // a query whose scores are all NaN or -inf never raised the maximum: its
+      // sum is then NaN (or 0), which decides the merged row
+      const bool none = l_acc[nb][0] == 0.f && m_run[nb] == kStart;
+      if (q4 == 0)
+        pm[nb * 16 + c16] = float2{none ? kNoKey : m_run[nb] * scale_log2e,
+                                   bad[nb] ? __builtin_nanf("") : l_acc[nb][0]};
+      if (none || !valid[nb]) continue;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) po[(nb * DB + db) * 64 + lane] = o[db][nb];
+    }
+    return;
+  }
   // ---- normalise and store: lane holds dims db*16 + q4*4 .. +3 of its query
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
@@ -804,6 +851,46 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
       *reinterpret_cast<u32x2*>(orow + db * 16 + q4 * 4) = w;
     }
   }
+}
+
+// Merges the S splits of attn_bf16_kernel<.., SPLIT>, in order of s: block x for
+// wave w of that kernel's grid, a wave per 16-dim block of one query block, 16
+// bytes per lane and split. A chain of two memory round trips: every split's
+// maximum and sum first, then the outputs of the splits that hold keys.
+template <int D>
+__global__ __launch_bounds__(256) void attn_merge_kernel(const f32x4* __restrict__ part, int R, int Hq,
+                                                         int Hkv, int G, int BR, int shift, int n_tiles,
+                                                         int splits, uint16_t* __restrict__ out) {
+  constexpr int DB = D / 16;
+  const int n_waves = gridDim.x;
+  const int w = blockIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int blk = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (threadIdx.x >> 6));   // (nb, db)
+  const int nb = blk / DB, db = blk % DB;
+  const int grp = (w >> 2) / n_tiles, tile = (w >> 2) - grp * n_tiles;
+  const int b = grp / Hkv, g = grp - b * Hkv;
+  const int m16 = (w & 3) * 32 + nb * 16 + (lane & 15);
+  const int rl = m16 / G, hh = m16 - rl * G;
+  const int r = tile * BR + rl - shift;
+  if (r < 0 || r >= R) return;
+  const float2* pm = reinterpret_cast<const float2*>(part + static_cast<size_t>(splits) * n_waves * (2 * DB * 64)) +
+                     w * 32 + nb * 16 + (lane & 15);
+  const f32x4* po = part + static_cast<size_t>(w) * (2 * DB * 64) + blk * 64 + lane;
+  float m = -INFINITY;
+#pragma unroll 4
+  for (int s = 0; s < splits; ++s) m = fmaxf(m, pm[s * n_waves * 32].x);
+  float l = 0.f;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int s = 0; s < splits; ++s) {
+    const float2 ml = pm[s * n_waves * 32];
+    const float wt = __builtin_amdgcn_exp2f(ml.x - m);
+    l += wt * ml.y;
+    if (ml.x > kNoKey) o += po[static_cast<size_t>(s) * n_waves * (2 * DB * 64)] * wt;
+  }
+  const float inv = 1.f / l;
+  const u32x2 v = {pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv)};
+  *reinterpret_cast<u32x2*>(out + ((static_cast<size_t>(b) * R + r) * Hq + g * G + hh) * D + db * 16 + (lane >> 4) * 4) = v;
 }
 
 // fp32 path: products on the matrix cores (v_mfma_f32_16x16x4_f32, fp32 in and
@@ -1037,10 +1124,50 @@ struct Paged {
   int max_pos;
 };
 
+// Splits of the key tiles of a bf16 call with R rows (1: not split): the number
+// with the least estimated time. A launch with fewer workgroups than the chip
+// has slots (2 per compute unit) is as long as its longest row, a serial chain
+// of N / 64 tiles (1.3 us each alone on a compute unit, 1.75 us beside another
+// workgroup, plus about 3 tiles of prologue and epilogue); splitting shortens
+// the chain and costs a second kernel and the partial outputs (fp32, written
+// and read, 66 KB per workgroup, 35 ns of the whole chip from cold memory). The
+// constants are fitted to 12 shapes x 1 .. 8 splits; a split has to promise 10%.
+// Measured (attention call, one request, 32 / 8 heads of 128; before -> after):
+// 344 rows of 2,080 tokens 45 -> 32 us, 506 of 3,008 61 -> 41 us, 874 of 8,160
+// 154 -> 99 us.
+int attention_splits(const rc_shape* s, int32_t R) {
+  const int G = s->Hq / s->Hkv;
+  if (s->dtype != RC_BF16 || R < 1 || kM % G != 0) return 1;
+  const double wgs = static_cast<double>(s->B) * s->Hkv * ((R + kM / G - 1) / (kM / G));
+  const double n = (s->N + kKT - 1) / kKT;
+  int best = 1;
+  double best_us = 0;
+  for (int p = 1; p <= kMaxSplits && wgs * p <= 1024 && p * kSplitTiles <= n; ++p) {
+    const double slots = wgs * p / 512;
+    const double tile = slots <= 0.5 ? 1.3 : slots < 1 ? 1.3 + 0.9 * (slots - 0.5) : 1.75;
+    const double chain = (n / p + 3) * tile;
+    const double work = wgs * (0.55 * n + 3 * p) * 1.75 / 512;   // rows see about half of the keys
+    const double us = p > 1 ? 1.1 * (max(chain, work) + 3 + 0.035 * wgs * p) : max(chain, work);
+    if (p == 1 || us < best_us) {
+      best = p;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
+int64_t attention_workspace(const rc_shape* s, int32_t R) {
+  const int splits = attention_splits(s, R);
+  if (splits == 1) return 0;
+  const int BR = kM / (s->Hq / s->Hkv);
+  return static_cast<int64_t>(splits) * s->B * s->Hkv * ((R + BR - 1) / BR) * kM * (s->D + 2) * 4;
+}
+
 // paged == nullptr: k, v are the assembled tensors; else the fresh tensors.
 int attention_impl(const rc_shape* shape, const void* q, const int32_t* rows, int32_t R,
                    const void* k, const void* v, float scale, void* out, float* lse,
-                   const Paged* paged, hipStream_t stream, const char* what, bool vref = false) {
+                   const Paged* paged, hipStream_t stream, const char* what, bool vref = false,
+                   void* ws = nullptr, int64_t ws_bytes = 0) {
   if (int st = check_shape(shape, true)) return st;
   if (R < 0) return fail(RC_ERR_INVALID_ARG, "R=%d must be >= 0", R);
   if (!q || !k || !v || (!out && R > 0))
@@ -1072,14 +1199,30 @@ int attention_impl(const rc_shape* shape, const void* q, const int32_t* rows, in
     dim3 grid(static_cast<unsigned>(blocks));
     const Paged none{};
     const Paged& pg = paged ? *paged : none;
+    const int splits = ws && !lse && reinterpret_cast<uintptr_t>(ws) % 16 == 0 &&
+                               attention_workspace(shape, R) <= ws_bytes
+                           ? attention_splits(shape, R)
+                           : 1;
+    grid.y = static_cast<unsigned>(splits);
     auto launch = [&](auto kern) {
       hipLaunchKernelGGL(kern, grid, dim3(kAttnThreads), 0, stream,
                          static_cast<const uint16_t*>(q), rows, R, N, Hq, Hkv, G, BR, n_tiles * BR - R,
                          static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v),
                          scale_log2e, static_cast<uint16_t*>(out), lse, n_tiles, n_groups, gpx,
-                         chunk, pg.pools, pg.segs, pg.S, pg.cos_t, pg.sin_t, pg.max_pos);
+                         chunk, pg.pools, pg.segs, pg.S, pg.cos_t, pg.sin_t, pg.max_pos, static_cast<float*>(ws));
     };
-    if (vref) {
+    if (splits > 1) {
+      if (vref) launch(attn_bf16_kernel<128, true, false, false, true, true>);
+      else if (paged && D == 128) launch(attn_bf16_kernel<128, true, false, true, false, true>);
+      else if (paged) launch(attn_bf16_kernel<64, true, false, true, false, true>);
+      else if (D == 128) launch(attn_bf16_kernel<128, true, false, false, false, true>);
+      else launch(attn_bf16_kernel<64, true, false, false, false, true>);
+      if (int st = check_launch(what)) return st;
+      const dim3 mg(static_cast<unsigned>(n_groups * n_tiles * 4), 2 * (D / 16) / 4);
+      hipLaunchKernelGGL((D == 128 ? attn_merge_kernel<128> : attn_merge_kernel<64>), mg, dim3(256), 0, stream,
+                         static_cast<const f32x4*>(ws), R, Hq, Hkv, G, BR, n_tiles * BR - R, n_tiles, splits,
+                         static_cast<uint16_t*>(out));
+    } else if (vref) {
       rows ? launch(attn_bf16_kernel<128, true, false, false, true>)
            : launch(attn_bf16_kernel<128, false, false, false, true>);
     } else if (paged) {
@@ -1124,6 +1267,20 @@ extern "C" int rc_selective_attention(const rc_shape* shape, const void* q, cons
                             "rc_selective_attention");
 }
 
+extern "C" int64_t rc_attention_workspace_bytes(const rc_shape* shape, int32_t R) {
+  if (!shape || shape->B < 1 || shape->N < 1 || shape->Hkv < 1 || shape->Hq % shape->Hkv) return 0;
+  return rc::attention_workspace(shape, R);
+}
+
+extern "C" int rc_selective_attention_ws(const rc_shape* shape, const void* q, const int32_t* rows,
+                                         int32_t R, const void* k, const void* v, float scale,
+                                         void* out, void* workspace, int64_t workspace_bytes,
+                                         hipStream_t stream) {
+  rc::clear_error();
+  return rc::attention_impl(shape, q, rows, R, k, v, scale, out, nullptr, nullptr, stream,
+                            "rc_selective_attention", false, workspace, workspace_bytes);
+}
+
 extern "C" int rc_selective_attention_lse(const rc_shape* shape, const void* q,
                                           const int32_t* rows, int32_t R, const void* k,
                                           const void* v, float scale, void* out, float* lse,
@@ -1134,23 +1291,31 @@ extern "C" int rc_selective_attention_lse(const rc_shape* shape, const void* q,
                             "rc_selective_attention_lse");
 }
 
-extern "C" int rc_selective_attention_vref(const rc_shape* shape, const void* q,
-                                           const int32_t* rows, int32_t R, const void* k,
-                                           const uint64_t* v_ref, float scale, void* out,
-                                           hipStream_t stream) {
+extern "C" int rc_selective_attention_vref_ws(const rc_shape* shape, const void* q,
+                                              const int32_t* rows, int32_t R, const void* k,
+                                              const uint64_t* v_ref, float scale, void* out,
+                                              void* workspace, int64_t workspace_bytes,
+                                              hipStream_t stream) {
   rc::clear_error();
   if (shape && (shape->dtype != RC_BF16 || shape->D != 128))
     return rc::fail(RC_ERR_UNSUPPORTED, "V rows by reference: bf16 with D = 128 only");
   return rc::attention_impl(shape, q, rows, R, k, v_ref, scale, out, nullptr, nullptr, stream,
-                            "rc_selective_attention_vref", true);
+                            "rc_selective_attention_vref", true, workspace, workspace_bytes);
 }
 
-extern "C" int rc_paged_attention(const rc_shape* shape, const void* q, const int32_t* rows,
-                                  int32_t R, const rc_pool* pools, int32_t n_pools,
-                                  const rc_segment* segs, int32_t S, const void* k_fresh,
-                                  const void* v_fresh, const float* rope_cos,
-                                  const float* rope_sin, int32_t max_pos, float scale, void* out,
-                                  hipStream_t stream) {
+extern "C" int rc_selective_attention_vref(const rc_shape* shape, const void* q,
+                                           const int32_t* rows, int32_t R, const void* k,
+                                           const uint64_t* v_ref, float scale, void* out,
+                                           hipStream_t stream) {
+  return rc_selective_attention_vref_ws(shape, q, rows, R, k, v_ref, scale, out, nullptr, 0, stream);
+}
+
+extern "C" int rc_paged_attention_ws(const rc_shape* shape, const void* q, const int32_t* rows,
+                                     int32_t R, const rc_pool* pools, int32_t n_pools,
+                                     const rc_segment* segs, int32_t S, const void* k_fresh,
+                                     const void* v_fresh, const float* rope_cos,
+                                     const float* rope_sin, int32_t max_pos, float scale, void* out,
+                                     void* workspace, int64_t workspace_bytes, hipStream_t stream) {
   using namespace rc;
   clear_error();
   if (int st = check_shape(shape, true)) return st;
@@ -1185,5 +1350,15 @@ extern "C" int rc_paged_attention(const rc_shape* shape, const void* q, const in
   pg.sin_t = rope_sin;
   pg.max_pos = rope_cos ? max_pos : 0;
   return attention_impl(shape, q, rows, R, k_fresh, v_fresh, scale, out, nullptr, &pg, stream,
-                        "rc_paged_attention");
+                        "rc_paged_attention", false, workspace, workspace_bytes);
+}
+
+extern "C" int rc_paged_attention(const rc_shape* shape, const void* q, const int32_t* rows,
+                                  int32_t R, const rc_pool* pools, int32_t n_pools,
+                                  const rc_segment* segs, int32_t S, const void* k_fresh,
+                                  const void* v_fresh, const float* rope_cos,
+                                  const float* rope_sin, int32_t max_pos, float scale, void* out,
+                                  hipStream_t stream) {
+  return rc_paged_attention_ws(shape, q, rows, R, pools, n_pools, segs, S, k_fresh, v_fresh, rope_cos,
+                               rope_sin, max_pos, scale, out, nullptr, 0, stream);
 }

@@ -75,6 +75,24 @@ def _shape(B, N, Hq, Hkv, D, dtype_code) -> RcShape:
     return RcShape(int(B), int(N), int(Hq), int(Hkv), int(D), int(dtype_code))
 
 
+def _workspace(nbytes: int, device, stream=None):
+    """Scratch memory of one call, from torch's allocator on the stream that
+    runs the call (so that it is reused only after it)."""
+    if nbytes == 0:
+        return None
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+def _attention_workspace(lib, shape: RcShape, R: int, device, stream=None):
+    """(tensor or None, address or None, bytes) of an attention call's scratch."""
+    nbytes = lib.rc_attention_workspace_bytes(ctypes.byref(shape), int(R))
+    ws = _workspace(nbytes, device, stream)
+    return ws, None if ws is None else ws.data_ptr(), nbytes
+
+
 # ---------------------------------------------------------------- segments
 
 @dataclass
@@ -306,10 +324,12 @@ def selective_attention_vref(q, k, v_ref, rows=None, scale=None, out=None, strea
     out = torch.empty((B, R, Hq, D), dtype=q.dtype, device=q.device) if out is None else out
     if DEBUG and rows is not None:
         check_rows(rows, N, "rc_selective_attention_vref")
-    check(_lib.load().rc_selective_attention_vref(
-        ctypes.byref(_shape(B, N, Hq, Hkv, D, _dtype_code(q))), _dev(q, "q"),
+    lib, shape = _lib.load(), _shape(B, N, Hq, Hkv, D, _dtype_code(q))
+    ws, ws_ptr, nbytes = _attention_workspace(lib, shape, R, q.device, stream)
+    check(lib.rc_selective_attention_vref_ws(
+        ctypes.byref(shape), _dev(q, "q"),
         None if rows is None else _dev(rows, "rows"), R, _dev(k, "k"), _dev(v_ref, "v_ref"),
-        ctypes.c_float(scale), _dev(out, "out"), _stream(stream)))
+        ctypes.c_float(scale), _dev(out, "out"), ws_ptr, nbytes, _stream(stream)))
     return out
 
 
@@ -326,10 +346,12 @@ def selective_attention(q, k, v, rows=None, scale=None, out=None, stream=None):
     out = torch.empty((B, R, Hq, D), dtype=q.dtype, device=q.device) if out is None else out
     if DEBUG and rows is not None:
         check_rows(rows, N, "rc_selective_attention")
-    check(_lib.load().rc_selective_attention(
-        ctypes.byref(_shape(B, N, Hq, Hkv, D, _dtype_code(q))), _dev(q, "q"),
+    lib, shape = _lib.load(), _shape(B, N, Hq, Hkv, D, _dtype_code(q))
+    ws, ws_ptr, nbytes = _attention_workspace(lib, shape, R, q.device, stream)
+    check(lib.rc_selective_attention_ws(
+        ctypes.byref(shape), _dev(q, "q"),
         None if rows is None else _dev(rows, "rows"), R, _dev(k, "k"), _dev(v, "v"),
-        ctypes.c_float(scale), _dev(out, "out"), _stream(stream)))
+        ctypes.c_float(scale), _dev(out, "out"), ws_ptr, nbytes, _stream(stream)))
     return out
 
 
@@ -420,12 +442,14 @@ def paged_attention(q, k_fresh, v_fresh, pools, segs: Segments, rows, cos=None, 
     out = torch.empty((B, R, Hq, D), dtype=q.dtype, device=q.device) if out is None else out
     parr = _pool_array(pools, k_fresh.dtype, Hkv, D)
     max_pos = 0 if cos is None else int(cos.shape[0])
-    check(_lib.load().rc_paged_attention(
-        ctypes.byref(_shape(B, N, Hq, Hkv, D, _dtype_code(q))), _dev(q, "q"), _dev(rows, "rows"), R,
+    lib, shape = _lib.load(), _shape(B, N, Hq, Hkv, D, _dtype_code(q))
+    ws, ws_ptr, nbytes = _attention_workspace(lib, shape, R, q.device, stream)
+    check(lib.rc_paged_attention_ws(
+        ctypes.byref(shape), _dev(q, "q"), _dev(rows, "rows"), R,
         parr, len(pools), _dev(segs.dev, "segs"), segs.S, _dev(k_fresh, "k_fresh"),
         _dev(v_fresh, "v_fresh"), None if cos is None else _dev(cos, "cos"),
         None if sin is None else _dev(sin, "sin"), max_pos, ctypes.c_float(scale),
-        _dev(out, "out"), _stream(stream)))
+        _dev(out, "out"), ws_ptr, nbytes, _stream(stream)))
     return out
 
 
@@ -621,17 +645,6 @@ def full_prefill(q, k_fresh, v_fresh, scale=None, out=None, stream=None):
 
 
 # ------------------------------------------------------- several layers
-
-def _workspace(nbytes: int, device, stream=None):
-    """Scratch memory of one call, from torch's allocator on the stream that
-    runs the call (so that it is reused only after it)."""
-    if nbytes == 0:
-        return None
-    if stream is None:
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
-    with torch.cuda.stream(stream):
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
-
 
 def gemm(x, w, residual=None, out=None, stream=None):
     """rc_gemm_bf16_ws: out[M, n] = x[M, k] @ w[n, k]^T (+ residual)."""

@@ -1,0 +1,133 @@
+"""bf16 attention divided over the keys (a workspace and few workgroups): against
+fp64 and the undivided call, and bit-identical across the assembled, the
+value-reference and the paged form."""
+import ctypes
+import math
+
+import pytest
+import torch
+
+from paper_2605_07443_amd import _lib, inputs, ops
+
+DEV = "cuda:0"
+
+
+def _bytes(B, N, Hq, Hkv, D, R, dtype=_lib.RC_BF16):
+    return _lib.load().rc_attention_workspace_bytes(ctypes.byref(_lib.RcShape(B, N, Hq, Hkv, D, dtype)), R)
+
+
+def test_workspace_rule():
+    assert _bytes(1, 2080, 32, 8, 128, 344) > 0
+    assert _bytes(1, 2080, 32, 8, 128, 344, _lib.RC_F32) == 0
+    assert _bytes(8, 3008, 32, 8, 128, 3008) == 0                 # fills the GPU by itself
+    assert _bytes(1, 191, 32, 8, 128, 40) == 0                    # under two splits of three tiles
+    assert _bytes(1, 2080, 32, 8, 128, 0) == 0 and _bytes(1, 2080, 3, 1, 128, 344) == 0
+    for R in (1, 31, 32, 33, 344, 2080):
+        per = 8 * -(-R // 32) * 128 * (128 + 2) * 4               # one split of every workgroup
+        b = _bytes(1, 2080, 32, 8, 128, R)
+        assert b % per == 0 and b // per in (0, 2, 3, 4, 5, 6, 7, 8), (R, b)
+
+
+def _inputs(B, N, Hq, Hkv, D, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    rn = lambda *s: torch.randn(s, generator=g, device=DEV).to(torch.bfloat16)  # noqa: E731
+    return rn(B, N, Hq, D), rn(B, N, Hkv, D), rn(B, N, Hkv, D)
+
+
+def _plain(q, k, v, rows):
+    B, N, Hq, D = q.shape
+    R = N if rows is None else rows.shape[1]
+    out = torch.empty((B, R, Hq, D), dtype=q.dtype, device=q.device)
+    vp = ctypes.c_void_p
+    _lib.check(_lib.load().rc_selective_attention(
+        ctypes.byref(_lib.RcShape(B, N, Hq, k.shape[2], D, _lib.RC_BF16)), vp(q.data_ptr()),
+        None if rows is None else vp(rows.data_ptr()), R, vp(k.data_ptr()), vp(v.data_ptr()),
+        ctypes.c_float(1 / math.sqrt(D)), vp(out.data_ptr()), vp(torch.cuda.current_stream().cuda_stream)))
+    return out
+
+
+def _ref(q, k, v, rows):
+    B, N, Hq, D = q.shape
+    G = Hq // k.shape[2]
+    outs = []
+    for b in range(B):
+        pos = torch.arange(N, device=q.device) if rows is None else rows[b].long()
+        kk, vv = (t[b].double().repeat_interleave(G, 1).permute(1, 0, 2).contiguous() for t in (k, v))
+        s = torch.matmul(q[b][pos].double().permute(1, 0, 2).contiguous(), kk.transpose(1, 2).contiguous()) / math.sqrt(D)
+        s.masked_fill_(torch.arange(N, device=q.device)[None, None] > pos[None, :, None], -math.inf)
+        outs.append(torch.matmul(torch.softmax(s, -1), vv).permute(1, 0, 2))
+    return torch.stack(outs)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,N,Hq,Hkv,D,R", [
+    (1, 513, 8, 2, 128, 33), (1, 449, 4, 4, 64, 50), (1, 1031, 4, 4, 64, 315), (1, 2080, 32, 8, 128, 344),
+    (2, 1500, 16, 4, 128, 1), (1, 1300, 64, 1, 64, 129), (1, 1999, 128, 1, 128, 40), (1, 1100, 4, 1, 128, 1100)])
+def test_split_against_fp64_and_undivided(B, N, Hq, Hkv, D, R):
+    print(f"[split] {B} {N} {Hq} {Hkv} {D} {R} bytes={_bytes(B, N, Hq, Hkv, D, R)}", flush=True)
+    assert _bytes(B, N, Hq, Hkv, D, R) > 0
+    q, k, v = _inputs(B, N, Hq, Hkv, D, N)
+    g = torch.Generator().manual_seed(R)
+    rows = None if R == N else torch.stack([torch.randperm(N, generator=g)[:R].sort().values for _ in range(B)]).to(torch.int32).to(DEV)
+    out, again, plain = ops.selective_attention(q, k, v, rows), ops.selective_attention(q, k, v, rows), _plain(q, k, v, rows)
+    want = _ref(q, k, v, rows)
+    torch.cuda.synchronize()
+    assert torch.equal(out, again)
+    for got in (out, plain):
+        # P and the output are rounded to bf16 (2^-9 each), as in the undivided call
+        assert (got.double() - want).norm().item() <= 4e-3 * want.norm().item()
+        assert (got.double() - want).abs().max().item() <= 2e-2
+
+
+@pytest.mark.gpu
+def test_split_rows_outside_and_non_finite_values():
+    """Row -1 / N are NaN; a NaN value reaches only rows that see its key."""
+    q, k, v = _inputs(1, 1024, 8, 2, 128, 7)
+    rows = torch.arange(0, 1024, 9, dtype=torch.int32, device=DEV)[None].contiguous()
+    assert _bytes(1, 1024, 8, 2, 128, rows.shape[1]) > 0
+    clean = ops.selective_attention(q, k, v, rows)
+    r2 = rows.clone()
+    r2[0, 5], r2[0, 9] = -1, 1024
+    out = ops.selective_attention(q, k, v, r2)
+    v2 = v.clone()
+    v2[:, 500] = math.nan
+    out2 = ops.selective_attention(q, k, v2, rows)
+    torch.cuda.synchronize()
+    assert torch.isnan(out[0, [5, 9]]).all()
+    keep = torch.ones(rows.shape[1], dtype=torch.bool, device=DEV)
+    keep[[5, 9]] = False
+    assert torch.isfinite(out[0, keep]).all()
+    before = rows[0] < 448   # rows of tiles that end before the NaN's tile
+    assert torch.equal(out2[0, before], clean[0, before])
+    assert torch.isnan(out2[0, rows[0] >= 500]).all()
+
+
+@pytest.mark.gpu
+def test_split_forms_are_bit_identical():
+    """One request: assembled copy, values by reference and paged, all divided
+    alike; a captured call replays to the same bits."""
+    cfg = inputs.WORKLOADS[2].with_(name="one", B=1, item_pool=200, hist_pool=4)
+    w = inputs.make(cfg, 3, device=DEV)
+    segs = ops.prepare_segments(w.segs, cfg.N, w.pools, DEV)
+    cos, sin = ops.rope_table(cfg.N, cfg.D, cfg.rope_base, DEV)
+    assert _bytes(1, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.R) > 0
+    args = (w.q, w.k_fresh, w.v_fresh, w.pools, segs, cfg.k, cos, sin)
+    a, b, c = ops.selective_prefill(*args), ops.selective_prefill_vref(*args), ops.paged_prefill(*args)
+    torch.cuda.synchronize()
+    assert torch.equal(a.rows, b.rows) and torch.equal(a.rows, c.rows)
+    assert torch.equal(a.out, b.out) and torch.equal(a.out, c.out)
+    out = torch.empty_like(a.out)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ops.selective_attention(w.q, a.k_asm, a.v_asm, a.rows, out=out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, a.out)
+        ops.selective_prefill(*args)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    d = ops.selective_attention(w.q, a.k_asm, a.v_asm, a.rows, out=torch.empty_like(a.out), stream=side)
+    side.synchronize()
+    assert torch.equal(d, a.out)
