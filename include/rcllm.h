@@ -326,8 +326,14 @@ int rc_selective_attention_vref(const rc_shape* shape, const void* q, const int3
  * workspace: device memory, 16-byte aligned, of
  * rc_attention_workspace_bytes(shape, R) bytes (host function; 0 where the call
  * is not divided, fp32 among it), used until `stream` has run the call. NULL or
- * a smaller one: the call is not divided. Errors: those of the call without. */
+ * a smaller one: the call is not divided. The paged call takes
+ * rc_paged_workspace_bytes(shape, S, R): where that pays off it aligns the keys
+ * of a few requests at a time (at most 96 MiB, or one request) into the
+ * workspace once instead of once per row tile; same outputs. Meant for rows
+ * spread over the prompt: for rows that see few keys (fresh rows at its start
+ * alone) call without a workspace. Errors: those of the call without. */
 int64_t rc_attention_workspace_bytes(const rc_shape* shape, int32_t R);
+int64_t rc_paged_workspace_bytes(const rc_shape* shape, int32_t S, int32_t R);
 int rc_selective_attention_ws(const rc_shape* shape, const void* q, const int32_t* rows, int32_t R,
                               const void* k, const void* v, float scale, void* out,
                               void* workspace, int64_t workspace_bytes, hipStream_t stream);

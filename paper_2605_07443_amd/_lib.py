@@ -28,7 +28,7 @@ EXPORTS = ("rc_rope_table", "rc_kv_assemble", "rc_rerope", "rc_select_tokens",
            "rc_gather_rows", "rc_kv_assemble_vref", "rc_select_tokens_vref",
            "rc_selective_attention_vref", "rc_gemm_workspace_bytes", "rc_gemm_bf16_ws",
            "rc_attention_workspace_bytes", "rc_selective_attention_ws",
-           "rc_selective_attention_vref_ws", "rc_paged_attention_ws",
+           "rc_selective_attention_vref_ws", "rc_paged_attention_ws", "rc_paged_workspace_bytes",
            "rc_status_string", "rc_last_error")
 
 
@@ -90,6 +90,7 @@ def load() -> ctypes.CDLL:
                                         vp]
     L.rc_selective_attention_vref.argtypes = [P(RcShape), vp, vp, i32, vp, vp, f32, vp, vp]
     L.rc_attention_workspace_bytes.argtypes = [P(RcShape), i32]
+    L.rc_paged_workspace_bytes.argtypes = [P(RcShape), i32, i32]
     for name in ("rc_selective_attention", "rc_selective_attention_vref", "rc_paged_attention"):
         args = list(getattr(L, name).argtypes)
         getattr(L, name + "_ws").argtypes = args[:-1] + [vp, i64, vp]
@@ -98,6 +99,7 @@ def load() -> ctypes.CDLL:
             getattr(L, name).restype = ctypes.c_int
     L.rc_gemm_workspace_bytes.restype = i64
     L.rc_attention_workspace_bytes.restype = i64
+    L.rc_paged_workspace_bytes.restype = i64
     L.rc_status_string.argtypes = [ctypes.c_int]
     L.rc_status_string.restype = ctypes.c_char_p
     L.rc_last_error.argtypes = []

@@ -86,9 +86,13 @@ def _workspace(nbytes: int, device, stream=None):
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
-def _attention_workspace(lib, shape: RcShape, R: int, device, stream=None):
-    """(tensor or None, address or None, bytes) of an attention call's scratch."""
-    nbytes = lib.rc_attention_workspace_bytes(ctypes.byref(shape), int(R))
+def _attention_workspace(lib, shape: RcShape, R: int, device, stream=None, paged_S: int = 0):
+    """(tensor or None, address or None, bytes) of an attention call's scratch
+    (paged_S: segments of the paged form)."""
+    if paged_S:
+        nbytes = lib.rc_paged_workspace_bytes(ctypes.byref(shape), int(paged_S), int(R))
+    else:
+        nbytes = lib.rc_attention_workspace_bytes(ctypes.byref(shape), int(R))
     ws = _workspace(nbytes, device, stream)
     return ws, None if ws is None else ws.data_ptr(), nbytes
 
@@ -308,8 +312,9 @@ def select_tokens_vref(segs: Segments, k: int, k_fresh, v_fresh, k_asm, v_ref, s
     return rows, (scores_out if scores_out is not None else scores_in)
 
 
-def selective_attention_vref(q, k, v_ref, rows=None, scale=None, out=None, stream=None):
-    """rc_selective_attention_vref: rc_selective_attention with V read
+def selective_attention_vref(q, k, v_ref, rows=None, scale=None, out=None, stream=None,
+                             divide=True):
+    """rc_selective_attention_vref_ws: rc_selective_attention_ws with V read
     through v_ref [B, N] int64 (value-row byte addresses); bf16, D = 128."""
     B, N, Hq, D = q.shape
     Hkv = k.shape[2]
@@ -325,7 +330,8 @@ def selective_attention_vref(q, k, v_ref, rows=None, scale=None, out=None, strea
     if DEBUG and rows is not None:
         check_rows(rows, N, "rc_selective_attention_vref")
     lib, shape = _lib.load(), _shape(B, N, Hq, Hkv, D, _dtype_code(q))
-    ws, ws_ptr, nbytes = _attention_workspace(lib, shape, R, q.device, stream)
+    ws, ws_ptr, nbytes = (_attention_workspace(lib, shape, R, q.device, stream) if divide
+                          else (None, None, 0))
     check(lib.rc_selective_attention_vref_ws(
         ctypes.byref(shape), _dev(q, "q"),
         None if rows is None else _dev(rows, "rows"), R, _dev(k, "k"), _dev(v_ref, "v_ref"),
@@ -333,8 +339,11 @@ def selective_attention_vref(q, k, v_ref, rows=None, scale=None, out=None, strea
     return out
 
 
-def selective_attention(q, k, v, rows=None, scale=None, out=None, stream=None):
-    """rc_selective_attention: causal GQA attention of `rows` (all rows if None)."""
+def selective_attention(q, k, v, rows=None, scale=None, out=None, stream=None,
+                        divide=True):
+    """rc_selective_attention_ws: causal GQA attention of `rows` (all rows if
+    None). divide=False: without a workspace (the keys of a small launch are
+    then not divided over workgroups), for rows that see few keys."""
     B, N, Hq, D = q.shape
     Hkv = k.shape[2]
     if k.shape != v.shape or k.shape[:2] != q.shape[:2] or k.shape[3] != D:
@@ -347,7 +356,8 @@ def selective_attention(q, k, v, rows=None, scale=None, out=None, stream=None):
     if DEBUG and rows is not None:
         check_rows(rows, N, "rc_selective_attention")
     lib, shape = _lib.load(), _shape(B, N, Hq, Hkv, D, _dtype_code(q))
-    ws, ws_ptr, nbytes = _attention_workspace(lib, shape, R, q.device, stream)
+    ws, ws_ptr, nbytes = (_attention_workspace(lib, shape, R, q.device, stream) if divide
+                          else (None, None, 0))
     check(lib.rc_selective_attention_ws(
         ctypes.byref(shape), _dev(q, "q"),
         None if rows is None else _dev(rows, "rows"), R, _dev(k, "k"), _dev(v, "v"),
@@ -430,9 +440,10 @@ def select_tokens_eq3(segs: Segments, item_mask: int, lam: float, k_hist: int, k
 
 
 def paged_attention(q, k_fresh, v_fresh, pools, segs: Segments, rows, cos=None, sin=None,
-                    scale=None, out=None, stream=None):
-    """rc_paged_attention: selective attention straight from the pools and
-    fresh tensors through the segment table (no assembled copy)."""
+                    scale=None, out=None, stream=None, divide=True):
+    """rc_paged_attention_ws: selective attention straight from the pools and
+    fresh tensors through the segment table (no assembled copy). divide=False:
+    without a workspace, for rows that see few keys."""
     B, N, Hq, D = q.shape
     Hkv = k_fresh.shape[2]
     if rows.dtype != torch.int32 or rows.dim() != 2 or rows.shape[0] != B:
@@ -443,7 +454,8 @@ def paged_attention(q, k_fresh, v_fresh, pools, segs: Segments, rows, cos=None, 
     parr = _pool_array(pools, k_fresh.dtype, Hkv, D)
     max_pos = 0 if cos is None else int(cos.shape[0])
     lib, shape = _lib.load(), _shape(B, N, Hq, Hkv, D, _dtype_code(q))
-    ws, ws_ptr, nbytes = _attention_workspace(lib, shape, R, q.device, stream)
+    ws, ws_ptr, nbytes = (_attention_workspace(lib, shape, R, q.device, stream, segs.S) if divide
+                          else (None, None, 0))
     check(lib.rc_paged_attention_ws(
         ctypes.byref(shape), _dev(q, "q"), _dev(rows, "rows"), R,
         parr, len(pools), _dev(segs.dev, "segs"), segs.S, _dev(k_fresh, "k_fresh"),
@@ -490,6 +502,17 @@ class PrefillBuffers:
             v_ref=torch.empty((B, N), dtype=torch.int64, device=device) if v_ref else None)
 
 
+def _spread(segs: Segments, k: int) -> bool:
+    """Whether the recomputed rows reach far into the prompt: with selected rows,
+    or with fresh positions in its second half. Rows at the start alone see few
+    keys, and the attention's workspace does not pay off (64 instruction rows of
+    one 8,160-token prompt: 7.4 us without it, 10.8 us with it)."""
+    if k > 0:
+        return True
+    h = segs.host
+    return bool(((h[..., 2] < 0) & (h[..., 0] + h[..., 1] > segs.N // 2)).any())
+
+
 def selective_prefill(q, k_fresh, v_fresh, pools, segs: Segments, k: int, cos, sin,
                       scale=None, bufs: PrefillBuffers | None = None, stream=None):
     """One layer of selective prefill on one stream: assemble (fused
@@ -506,7 +529,7 @@ def selective_prefill(q, k_fresh, v_fresh, pools, segs: Segments, k: int, cos, s
     select_tokens(segs, k, k_fresh, v_fresh, bufs.k_asm, bufs.v_asm, scores_in=bufs.scores,
                   rows_out=bufs.rows, patch=True, stream=stream)
     if R > 0:
-        selective_attention(q, bufs.k_asm, bufs.v_asm, bufs.rows, scale, bufs.out, stream)
+        selective_attention(q, bufs.k_asm, bufs.v_asm, bufs.rows, scale, bufs.out, stream, _spread(segs, k))
     return bufs
 
 
@@ -529,7 +552,8 @@ def selective_prefill_vref(q, k_fresh, v_fresh, pools, segs: Segments, k: int, c
     select_tokens_vref(segs, k, k_fresh, v_fresh, bufs.k_asm, bufs.v_ref, scores_in=bufs.scores,
                        rows_out=bufs.rows, stream=stream)
     if R > 0:
-        selective_attention_vref(q, bufs.k_asm, bufs.v_ref, bufs.rows, scale, bufs.out, stream)
+        selective_attention_vref(q, bufs.k_asm, bufs.v_ref, bufs.rows, scale, bufs.out, stream,
+                                 _spread(segs, k))
     return bufs
 
 
@@ -593,7 +617,7 @@ def paged_prefill(q, k_fresh, v_fresh, pools, segs: Segments, k: int, cos, sin, 
                   patch=False, stream=stream)
     if R > 0:
         paged_attention(q, k_fresh, v_fresh, pools, segs, bufs.rows, cos, sin, scale, bufs.out,
-                        stream)
+                        stream, _spread(segs, k))
     return bufs
 
 

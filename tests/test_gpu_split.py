@@ -131,3 +131,38 @@ def test_split_forms_are_bit_identical():
     d = ops.selective_attention(w.q, a.k_asm, a.v_asm, a.rows, out=torch.empty_like(a.out), stream=side)
     side.synchronize()
     assert torch.equal(d, a.out)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,rot", [(8, True), (7, False)])
+def test_paged_keys_staged_a_few_requests_at_a_time(B, rot):
+    """More keys than one stage holds (96 MiB: six requests of 8,160 tokens):
+    the paged form equals the assembled one bit for bit, with listed rows
+    outside the prompt too."""
+    cfg = inputs.WORKLOADS[3].with_(name="staged", B=B, item_pool=120, hist_pool=3, pct=2)
+    w = inputs.make(cfg, 4, device=DEV)
+    segs = ops.prepare_segments(w.segs, cfg.N, w.pools, DEV)
+    cos, sin = ops.rope_table(cfg.N, cfg.D, cfg.rope_base, DEV) if rot else (None, None)
+    shape = _lib.RcShape(B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, _lib.RC_BF16)
+    b = _lib.load().rc_paged_workspace_bytes(ctypes.byref(shape), segs.S, cfg.R)
+    per = cfg.N * cfg.Hkv * cfg.D * 2
+    assert 6 * per < b < 7 * per + _bytes(6, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.R) + (80 << 20) and B > 6
+    assert _lib.load().rc_paged_workspace_bytes(ctypes.byref(shape), 65, cfg.R) in (
+        0, _bytes(B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.R))
+    k_asm, v_asm = ops.kv_assemble(w.pools, segs, w.k_fresh, w.v_fresh, cos, sin)
+    rows, _ = ops.select_tokens(segs, cfg.k, w.k_fresh, w.v_fresh, k_asm, v_asm)
+    rows = rows.clone()
+    rows[0, 3], rows[B - 1, 0] = -1, cfg.N
+    a = ops.selective_attention(w.q, k_asm, v_asm, rows)
+    p = ops.paged_attention(w.q, w.k_fresh, w.v_fresh, w.pools, segs, rows, cos, sin)
+    u = ops.paged_attention(w.q, w.k_fresh, w.v_fresh, w.pools, segs, rows, cos, sin, divide=False)
+    torch.cuda.synchronize()
+    # rows 3 of request 0 and 0 of the last are NaN in all three; the assembled
+    # cache holds those positions' fresh rows (selected when it was patched), the
+    # paged one the pool rows, so these two requests are compared on the others
+    assert torch.isnan(p[0, 3]).all() and torch.isnan(p[B - 1, 0]).all()
+    assert torch.equal(p[1:B - 1], a[1:B - 1])
+    # the paged kernel, not divided: the same up to the rounding of P and the output
+    ok = ~torch.isnan(p)
+    assert torch.equal(torch.isnan(u), ~ok)
+    assert (p[ok].float() - u[ok].float()).norm().item() <= 4e-3 * p[ok].float().norm().item()
