@@ -599,8 +599,10 @@ bool gemm_tiles_ok(int k, const void* x, const void* w) {
          reinterpret_cast<uintptr_t>(w) % 16 == 0;
 }
 
+// planned: by gemm_plan, within the workspace (which may be absent because the
+// plan needs none); else the rule of rc_gemm_bf16, which borrows rows of y.
 int gemm_impl(int64_t M, int32_t n, int32_t k, const void* x, const void* w, const void* residual,
-              void* y, void* workspace, int64_t workspace_bytes, hipStream_t stream) {
+              void* y, bool planned, void* workspace, int64_t workspace_bytes, hipStream_t stream) {
   if (!x || !w || !y) return fail(RC_ERR_INVALID_ARG, "x, w and y must be non-NULL");
   if (M < 0 || n < 1 || k < 8 || k % 8)
     return fail(RC_ERR_INVALID_ARG, "M=%lld n=%d k=%d (k a positive multiple of 8)",
@@ -638,8 +640,8 @@ int gemm_impl(int64_t M, int32_t n, int32_t k, const void* x, const void* w, con
   float* part = static_cast<float*>(workspace);
   const bool have = workspace && reinterpret_cast<uintptr_t>(workspace) % 16 == 0;
   GemmPlan plan = gemm_plan(M, n, k, have ? min(workspace_bytes, kGMaxWorkspace) : 0);
-  if (!have && M >= kBM && n >= kBN && M % kBM != 0) {
-    // without a workspace: the whole 256-row tiles on the largest tile; the
+  if (!planned && M >= kBM && n >= kBN && M % kBM != 0) {
+    // the whole 256-row tiles on the largest tile; the
     // remaining rows split over k, when the middle tile would run them on few
     // workgroups, with their partial sums in the first rows of y, which the
     // large tiles overwrite afterwards on the same stream (about 512
@@ -674,7 +676,7 @@ int gemm_impl(int64_t M, int32_t n, int32_t k, const void* x, const void* w, con
 extern "C" int rc_gemm_bf16(int64_t M, int32_t n, int32_t k, const void* x, const void* w,
                             const void* residual, void* y, hipStream_t stream) {
   rc::clear_error();
-  return rc::gemm_impl(M, n, k, x, w, residual, y, nullptr, 0, stream);
+  return rc::gemm_impl(M, n, k, x, w, residual, y, false, nullptr, 0, stream);
 }
 
 extern "C" int64_t rc_gemm_workspace_bytes(int64_t M, int32_t n, int32_t k) {
@@ -686,5 +688,5 @@ extern "C" int rc_gemm_bf16_ws(int64_t M, int32_t n, int32_t k, const void* x, c
                                const void* residual, void* y, void* workspace,
                                int64_t workspace_bytes, hipStream_t stream) {
   rc::clear_error();
-  return rc::gemm_impl(M, n, k, x, w, residual, y, workspace, workspace_bytes, stream);
+  return rc::gemm_impl(M, n, k, x, w, residual, y, true, workspace, workspace_bytes, stream);
 }
