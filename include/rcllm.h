@@ -347,6 +347,27 @@ int rc_paged_attention_ws(const rc_shape* shape, const void* q, const int32_t* r
                           const float* rope_sin, int32_t max_pos, float scale, void* out,
                           void* workspace, int64_t workspace_bytes, hipStream_t stream);
 
+/* One layer of selective prefill in one call (Sec. III-C.3): the calls of one
+ * chain, enqueued in order on `stream` with the same results.
+ *   RC_CHAIN_COPY   rc_kv_assemble (scores into `scores`), rc_select_tokens with
+ *                   scores_in = scores and patch = 1, rc_selective_attention_ws
+ *   RC_CHAIN_VREF   the same with rc_kv_assemble_vref, rc_select_tokens_vref and
+ *                   rc_selective_attention_vref_ws; v_out is the table v_ref
+ *   RC_CHAIN_PAGED  rc_kv_assemble scoring only, rc_select_tokens without patch,
+ *                   rc_paged_attention_ws; k_asm and v_out are not used
+ * Arguments as in those calls; rows holds n_fresh + k entries per request, and
+ * with none the attention is left out. workspace: that of the attention call
+ * (rc_attention_workspace_bytes, rc_paged_workspace_bytes with R = n_fresh + k),
+ * or NULL.
+ * Errors: those of the calls; what came before the failing one is enqueued. */
+typedef enum { RC_CHAIN_COPY = 0, RC_CHAIN_VREF = 1, RC_CHAIN_PAGED = 2 } rc_chain;
+int rc_selective_prefill(const rc_shape* shape, int32_t chain, const rc_pool* pools,
+                         int32_t n_pools, const rc_segment* segs, int32_t S, int32_t n_fresh,
+                         int32_t k, const void* q, const void* k_fresh, const void* v_fresh,
+                         const float* rope_cos, const float* rope_sin, int32_t max_pos,
+                         float scale, void* k_asm, void* v_out, float* scores, int32_t* rows,
+                         void* out, void* workspace, int64_t workspace_bytes, hipStream_t stream);
+
 /* Attention-mass term of Eq. (3) (Sec. III-C.2b: the first layer is computed
  * in full and a token's importance includes the attention weight it
  * receives). For KV group g and position j of request b:

@@ -19,6 +19,7 @@ LIB_PATH = os.environ.get("RCLLM_LIB") or os.path.join(PKG, "librcllm.so")
 
 RC_OK, RC_ERR_INVALID_ARG, RC_ERR_UNSUPPORTED, RC_ERR_HIP = 0, -1, -2, -3
 RC_F32, RC_BF16 = 0, 1
+RC_CHAIN_COPY, RC_CHAIN_VREF, RC_CHAIN_PAGED = 0, 1, 2
 
 # every symbol include/rcllm.h declares
 EXPORTS = ("rc_rope_table", "rc_kv_assemble", "rc_rerope", "rc_select_tokens",
@@ -29,6 +30,7 @@ EXPORTS = ("rc_rope_table", "rc_kv_assemble", "rc_rerope", "rc_select_tokens",
            "rc_selective_attention_vref", "rc_gemm_workspace_bytes", "rc_gemm_bf16_ws",
            "rc_attention_workspace_bytes", "rc_selective_attention_ws",
            "rc_selective_attention_vref_ws", "rc_paged_attention_ws", "rc_paged_workspace_bytes",
+           "rc_selective_prefill",
            "rc_status_string", "rc_last_error")
 
 
@@ -90,6 +92,8 @@ def load() -> ctypes.CDLL:
                                         vp]
     L.rc_selective_attention_vref.argtypes = [P(RcShape), vp, vp, i32, vp, vp, f32, vp, vp]
     L.rc_attention_workspace_bytes.argtypes = [P(RcShape), i32]
+    L.rc_selective_prefill.argtypes = [P(RcShape), i32, P(RcPool), i32, vp, i32, i32, i32, vp, vp, vp,
+                                       vp, vp, i32, f32, vp, vp, vp, vp, vp, vp, i64, vp]
     L.rc_paged_workspace_bytes.argtypes = [P(RcShape), i32, i32]
     for name in ("rc_selective_attention", "rc_selective_attention_vref", "rc_paged_attention"):
         args = list(getattr(L, name).argtypes)

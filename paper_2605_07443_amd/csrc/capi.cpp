@@ -83,6 +83,51 @@ int rc_rope_table(int32_t max_pos, int32_t D, double base, float* cos_out, float
   return RC_OK;
 }
 
+// The three calls of a chain from one host call: a step of a few small kernels
+// is bound by what the host does per call (about 10 us each through the Python
+// binding, of which 2 us are the launch).
+int rc_selective_prefill(const rc_shape* shape, int32_t chain, const rc_pool* pools,
+                         int32_t n_pools, const rc_segment* segs, int32_t S, int32_t n_fresh,
+                         int32_t k, const void* q, const void* k_fresh, const void* v_fresh,
+                         const float* rope_cos, const float* rope_sin, int32_t max_pos,
+                         float scale, void* k_asm, void* v_out, float* scores, int32_t* rows,
+                         void* out, void* workspace, int64_t workspace_bytes, hipStream_t stream) {
+  rc::clear_error();
+  if (chain != RC_CHAIN_COPY && chain != RC_CHAIN_VREF && chain != RC_CHAIN_PAGED)
+    return rc::fail(RC_ERR_INVALID_ARG, "chain=%d", chain);
+  if (!scores) return rc::fail(RC_ERR_INVALID_ARG, "scores must be non-NULL");
+  if (chain != RC_CHAIN_PAGED && (!k_asm || !v_out))
+    return rc::fail(RC_ERR_INVALID_ARG, "k_asm and v_out must be non-NULL");
+  uint64_t* v_ref = static_cast<uint64_t*>(v_out);
+  int st;
+  if (chain == RC_CHAIN_VREF)
+    st = rc_kv_assemble_vref(shape, pools, n_pools, segs, S, k_fresh, v_fresh, rope_cos, rope_sin, max_pos,
+                             k_asm, v_ref, scores, stream);
+  else
+    st = rc_kv_assemble(shape, pools, n_pools, segs, S, k_fresh, v_fresh, rope_cos, rope_sin, max_pos,
+                        chain == RC_CHAIN_PAGED ? nullptr : k_asm, chain == RC_CHAIN_PAGED ? nullptr : v_out,
+                        scores, stream);
+  if (st) return st;
+  if (chain == RC_CHAIN_VREF)
+    st = rc_select_tokens_vref(shape, segs, S, n_fresh, k, k_fresh, v_fresh, k_asm, v_ref, scores, nullptr,
+                               rows, stream);
+  else
+    st = rc_select_tokens(shape, segs, S, n_fresh, k, k_fresh, v_fresh,
+                          chain == RC_CHAIN_PAGED ? nullptr : k_asm, chain == RC_CHAIN_PAGED ? nullptr : v_out,
+                          scores, nullptr, rows, chain == RC_CHAIN_PAGED ? 0 : 1, stream);
+  if (st) return st;
+  const int32_t R = n_fresh + k;
+  if (R == 0) return RC_OK;
+  if (chain == RC_CHAIN_VREF)
+    return rc_selective_attention_vref_ws(shape, q, rows, R, k_asm, v_ref, scale, out, workspace,
+                                          workspace_bytes, stream);
+  if (chain == RC_CHAIN_COPY)
+    return rc_selective_attention_ws(shape, q, rows, R, k_asm, v_out, scale, out, workspace, workspace_bytes,
+                                     stream);
+  return rc_paged_attention_ws(shape, q, rows, R, pools, n_pools, segs, S, k_fresh, v_fresh, rope_cos, rope_sin,
+                               max_pos, scale, out, workspace, workspace_bytes, stream);
+}
+
 // The local sliding window (Sec. III-C.2b): the last W positions of every
 // request are recomputed like instruction tokens, so they become fresh
 // segments. Segments before N - W are kept, the one crossing N - W is cut

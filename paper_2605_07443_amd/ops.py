@@ -513,6 +513,46 @@ def _spread(segs: Segments, k: int) -> bool:
     return bool(((h[..., 2] < 0) & (h[..., 0] + h[..., 1] > segs.N // 2)).any())
 
 
+def _chain(chain: int, q, k_fresh, v_fresh, pools, segs: Segments, k: int, cos, sin, scale,
+           bufs: PrefillBuffers, stream) -> None:
+    """rc_selective_prefill over checked buffers: the whole step in one call."""
+    B, N, Hq, D = q.shape
+    Hkv = k_fresh.shape[2]
+    k = int(k)
+    R = segs.n_fresh + k
+    if v_fresh.shape != k_fresh.shape or v_fresh.dtype != k_fresh.dtype:
+        raise ValueError("k_fresh and v_fresh must match")
+    if k_fresh.shape[0] != B or k_fresh.shape[1] != N or k_fresh.shape[3] != D or k_fresh.dtype != q.dtype:
+        raise ValueError("q [B,N,Hq,D] and k_fresh, v_fresh [B,N,Hkv,D] do not match")
+    if bufs.rows.dtype != torch.int32 or tuple(bufs.rows.shape) != (B, R):
+        raise ValueError("rows must be int32 [B, n_fresh + k]")
+    k_ptr = v_ptr = None
+    if chain != _lib.RC_CHAIN_PAGED:
+        v_buf = bufs.v_asm if chain == _lib.RC_CHAIN_COPY else bufs.v_ref
+        if bufs.k_asm.shape != k_fresh.shape:
+            raise ValueError("k_asm must be [B,N,Hkv,D]")
+        if chain == _lib.RC_CHAIN_COPY:
+            if v_buf.shape != k_fresh.shape:
+                raise ValueError("v_asm must be [B,N,Hkv,D]")
+        elif v_buf.dtype != torch.int64 or tuple(v_buf.shape) != (B, N):
+            raise ValueError("v_ref must be int64 [B, N]")
+        k_ptr, v_ptr = _dev(bufs.k_asm, "k_asm"), _dev(v_buf, "v_out")
+    lib = _lib.load()
+    shape = RcShape(B, N, Hq, Hkv, D, _dtype_code(q))
+    ws, ws_ptr, nbytes = None, None, 0
+    if R > 0 and _spread(segs, k):
+        ws, ws_ptr, nbytes = _attention_workspace(lib, shape, R, q.device, stream,
+                                                  segs.S if chain == _lib.RC_CHAIN_PAGED else 0)
+    check(lib.rc_selective_prefill(
+        ctypes.byref(shape), chain, _pool_array(pools, k_fresh.dtype, Hkv, D), len(pools),
+        _dev(segs.dev, "segs"), segs.S, segs.n_fresh, k, _dev(q, "q"), _dev(k_fresh, "k_fresh"),
+        _dev(v_fresh, "v_fresh"), None if cos is None else _dev(cos, "cos"),
+        None if sin is None else _dev(sin, "sin"), 0 if cos is None else int(cos.shape[0]),
+        1.0 / math.sqrt(D) if scale is None else float(scale), k_ptr, v_ptr,
+        _dev(bufs.scores, "scores"), _dev(bufs.rows, "rows"), _dev(bufs.out, "out"), ws_ptr, nbytes,
+        _stream(stream)))
+
+
 def selective_prefill(q, k_fresh, v_fresh, pools, segs: Segments, k: int, cos, sin,
                       scale=None, bufs: PrefillBuffers | None = None, stream=None):
     """One layer of selective prefill on one stream: assemble (fused
@@ -524,6 +564,9 @@ def selective_prefill(q, k_fresh, v_fresh, pools, segs: Segments, k: int, cos, s
     R = segs.n_fresh + int(k)
     if bufs is None:
         bufs = PrefillBuffers.alloc(B, N, Hq, Hkv, D, R, q.dtype, q.device)
+    if not DEBUG:
+        _chain(_lib.RC_CHAIN_COPY, q, k_fresh, v_fresh, pools, segs, k, cos, sin, scale, bufs, stream)
+        return bufs
     kv_assemble(pools, segs, k_fresh, v_fresh, cos, sin, bufs.k_asm, bufs.v_asm,
                 scores_out=bufs.scores, stream=stream)
     select_tokens(segs, k, k_fresh, v_fresh, bufs.k_asm, bufs.v_asm, scores_in=bufs.scores,
@@ -547,6 +590,9 @@ def selective_prefill_vref(q, k_fresh, v_fresh, pools, segs: Segments, k: int, c
     if bufs is None:
         bufs = PrefillBuffers.alloc(B, N, Hq, Hkv, D, R, q.dtype, q.device, v_copy=False,
                                     v_ref=True)
+    if not DEBUG:
+        _chain(_lib.RC_CHAIN_VREF, q, k_fresh, v_fresh, pools, segs, k, cos, sin, scale, bufs, stream)
+        return bufs
     kv_assemble_vref(pools, segs, k_fresh, v_fresh, cos, sin, bufs.k_asm, bufs.v_ref,
                      scores_out=bufs.scores, stream=stream)
     select_tokens_vref(segs, k, k_fresh, v_fresh, bufs.k_asm, bufs.v_ref, scores_in=bufs.scores,
@@ -611,6 +657,9 @@ def paged_prefill(q, k_fresh, v_fresh, pools, segs: Segments, k: int, cos, sin, 
     R = segs.n_fresh + int(k)
     if bufs is None:
         bufs = PrefillBuffers.alloc(B, N, Hq, Hkv, D, R, q.dtype, q.device)
+    if not DEBUG:
+        _chain(_lib.RC_CHAIN_PAGED, q, k_fresh, v_fresh, pools, segs, k, cos, sin, scale, bufs, stream)
+        return bufs
     kv_assemble(pools, segs, k_fresh, v_fresh, cos, sin, scores_out=bufs.scores, stream=stream,
                 score_only=True)
     select_tokens(segs, k, k_fresh, v_fresh, None, None, scores_in=bufs.scores, rows_out=bufs.rows,

@@ -1,0 +1,77 @@
+"""rc_selective_prefill (one call for a whole step) against the calls it stands
+for, and its argument checks."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2605_07443_amd import _lib, inputs, ops
+
+DEV = "cuda:0"
+
+
+@pytest.mark.skipif(torch.cuda.device_count() > 0, reason="fake pointers: hosts without a GPU only")
+def test_chain_rejects_bad_arguments_on_the_host():
+    lib = _lib.load()
+    shape = ctypes.byref(_lib.RcShape(1, 64, 8, 2, 128, 1))
+    pools = (_lib.RcPool * 1)(_lib.RcPool(4096, 8192, 2, 64))
+
+    def call(chain=0, k_asm=1 << 20, v_out=2 << 20, scores=3 << 20, S=1, k=1, n_fresh=0):
+        return lib.rc_selective_prefill(shape, chain, pools, 1, 4 << 20, S, n_fresh, k, 5 << 20, 6 << 20, 7 << 20,
+                                        None, None, 0, 0.1, k_asm, v_out, scores, 8 << 20, 9 << 20, None, 0, None)
+
+    assert call(chain=3) == _lib.RC_ERR_INVALID_ARG
+    assert call(scores=None) == _lib.RC_ERR_INVALID_ARG
+    for chain in (_lib.RC_CHAIN_COPY, _lib.RC_CHAIN_VREF):
+        assert call(chain, k_asm=None) == _lib.RC_ERR_INVALID_ARG
+        assert call(chain, v_out=None) == _lib.RC_ERR_INVALID_ARG
+    for chain in (0, 1, 2):
+        assert call(chain, S=0) == _lib.RC_ERR_INVALID_ARG
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,pct", [("tiny-bf16", 15), ("ragged-bf16", 0), ("mha-d64-bf16", 100),
+                                      ("tiny-f32-gqa", 25), ("allfresh-bf16", 15)])
+def test_chain_equals_its_calls(name, pct):
+    cfg = inputs.TEST_WORKLOADS[name]
+    w = inputs.make(cfg, 2, device=DEV)
+    segs = ops.prepare_segments(w.segs, cfg.N, w.pools, DEV)
+    cos, sin = ops.rope_table(cfg.N, cfg.D, cfg.rope_base, DEV)
+    k = cfg.k_for(pct)
+    scores = torch.empty((cfg.B, cfg.N), dtype=torch.float32, device=DEV)
+    k_asm, v_asm = ops.kv_assemble(w.pools, segs, w.k_fresh, w.v_fresh, cos, sin, scores_out=scores)
+    rows, _ = ops.select_tokens(segs, k, w.k_fresh, w.v_fresh, k_asm, v_asm, scores_in=scores)
+    out = ops.selective_attention(w.q, k_asm, v_asm, rows) if rows.shape[1] else None
+    args = (w.q, w.k_fresh, w.v_fresh, w.pools, segs, k, cos, sin)
+    a = ops.selective_prefill(*args)
+    same = [a]
+    torch.cuda.synchronize()
+    assert torch.equal(a.k_asm, k_asm) and torch.equal(a.v_asm, v_asm)
+    if cfg.D == 128:
+        same.append(ops.selective_prefill_vref(*args))
+    if cfg.dtype == "bf16":
+        same.append(ops.paged_prefill(*args))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    same.append(ops.selective_prefill(*args, stream=side))
+    side.synchronize()
+    torch.cuda.synchronize()
+    for b in same:
+        assert torch.equal(b.scores, scores) and torch.equal(b.rows, rows)
+        if out is not None:
+            # divided alike when the keys are divided at all (k > 0)
+            assert torch.equal(b.out, same[0].out)
+            assert (b.out.float() - out.float()).norm().item() <= 4e-3 * out.float().norm().item()
+
+
+@pytest.mark.gpu
+def test_chain_refuses_buffers_of_another_shape():
+    cfg = inputs.TEST_WORKLOADS["tiny-bf16"]
+    w = inputs.make(cfg, 2, device=DEV)
+    segs = ops.prepare_segments(w.segs, cfg.N, w.pools, DEV)
+    cos, sin = ops.rope_table(cfg.N, cfg.D, cfg.rope_base, DEV)
+    bufs = ops.PrefillBuffers.alloc(cfg.B, cfg.N, cfg.Hq, cfg.Hkv, cfg.D, cfg.R + 1, torch.bfloat16, DEV)
+    with pytest.raises(ValueError):
+        ops.selective_prefill(w.q, w.k_fresh, w.v_fresh, w.pools, segs, cfg.k, cos, sin, bufs=bufs)
+    with pytest.raises(ValueError):
+        ops.selective_prefill(w.q, w.k_fresh, w.v_fresh[:1], w.pools, segs, cfg.k, cos, sin)
