@@ -385,6 +385,18 @@ int rc_selective_prefill(const rc_shape* shape, int32_t chain, const rc_pool* po
 int rc_attention_mass(const rc_shape* shape, const void* q, const void* k, const float* lse,
                       float scale, float* mass, hipStream_t stream);
 
+/* rc_attention_mass with a workspace: a bf16 call divides the rows that each
+ * block of keys sums over several workgroups and adds their sums in a fixed
+ * order (deterministic; the order of the fp32 sum depends on whether the
+ * workspace is given). workspace: device memory, 4-byte aligned, of
+ * rc_mass_workspace_bytes(shape) bytes (host function; 0 where nothing is
+ * divided), used until `stream` has run the call. NULL or a smaller one: not
+ * divided. Errors: those of rc_attention_mass. */
+int64_t rc_mass_workspace_bytes(const rc_shape* shape);
+int rc_attention_mass_ws(const rc_shape* shape, const void* q, const void* k, const float* lse,
+                         float scale, float* mass, void* workspace, int64_t workspace_bytes,
+                         hipStream_t stream);
+
 /* Heavy-hitter selection by the full score of Eq. (3), with separate budgets
  * for history and item tokens (recompute ratios r_rev and r_item, Sec. IV-A),
  * and correction (Sec. III-C.3 (iii)).

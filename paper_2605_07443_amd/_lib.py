@@ -30,7 +30,7 @@ EXPORTS = ("rc_rope_table", "rc_kv_assemble", "rc_rerope", "rc_select_tokens",
            "rc_selective_attention_vref", "rc_gemm_workspace_bytes", "rc_gemm_bf16_ws",
            "rc_attention_workspace_bytes", "rc_selective_attention_ws",
            "rc_selective_attention_vref_ws", "rc_paged_attention_ws", "rc_paged_workspace_bytes",
-           "rc_selective_prefill",
+           "rc_selective_prefill", "rc_mass_workspace_bytes", "rc_attention_mass_ws",
            "rc_status_string", "rc_last_error")
 
 
@@ -92,6 +92,8 @@ def load() -> ctypes.CDLL:
                                         vp]
     L.rc_selective_attention_vref.argtypes = [P(RcShape), vp, vp, i32, vp, vp, f32, vp, vp]
     L.rc_attention_workspace_bytes.argtypes = [P(RcShape), i32]
+    L.rc_mass_workspace_bytes.argtypes = [P(RcShape)]
+    L.rc_attention_mass_ws.argtypes = [P(RcShape), vp, vp, vp, f32, vp, vp, i64, vp]
     L.rc_selective_prefill.argtypes = [P(RcShape), i32, P(RcPool), i32, vp, i32, i32, i32, vp, vp, vp,
                                        vp, vp, i32, f32, vp, vp, vp, vp, vp, vp, i64, vp]
     L.rc_paged_workspace_bytes.argtypes = [P(RcShape), i32, i32]
@@ -104,6 +106,7 @@ def load() -> ctypes.CDLL:
     L.rc_gemm_workspace_bytes.restype = i64
     L.rc_attention_workspace_bytes.restype = i64
     L.rc_paged_workspace_bytes.restype = i64
+    L.rc_mass_workspace_bytes.restype = i64
     L.rc_status_string.argtypes = [ctypes.c_int]
     L.rc_status_string.restype = ctypes.c_char_p
     L.rc_last_error.argtypes = []

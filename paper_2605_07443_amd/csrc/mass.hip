@@ -22,6 +22,11 @@
 //     atomics are needed and the result is deterministic.
 //   * Workgroups of one group run on one XCD (ids are dealt round-robin over
 //     the 8 XCDs), longest (earliest) key blocks first.
+//   * With a workspace the query tiles of a key block are divided over several
+//     workgroups (blockIdx.y), whose sums mass_sum_kernel adds in order: the
+//     first key block sees every query and would otherwise outlast the launch
+//     (12 units of 256 queries against 9.75 per slot on average for 8 prompts of
+//     3,008), and one request alone leaves most of the GPU idle.
 // fp32 path: mass_f32_kernel below.
 #include <cmath>
 #include <type_traits>
@@ -63,6 +68,7 @@ void mass_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
                       const float* __restrict__ lse, int N, int Hq, int Hkv, int G,
                       int g_shift, float scale_log2e, float* __restrict__ mass, int n_kblk,
                       int n_groups, int gpx) {
+  // part blockIdx.y of the query tiles writes its own [B, Hkv, N] block
   constexpr int DC = D / 32;                       // 32-wide d chunks
   constexpr int UPR = D / 8;                       // 16-byte units per query row
   constexpr int QU = kQV * UPR / kMassThreads;     // staged units per thread
@@ -87,7 +93,9 @@ void mass_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
   const int QP = kQV / G;                 // positions per tile
   const int p_begin = kblk * kMassKeys;   // first row that sees a key of the block
   const int j0 = p_begin + wave * 64;     // this wave's first key
-  const int n_qt = (N - p_begin + QP - 1) / QP;
+  const int tiles = (N - p_begin + QP - 1) / QP;
+  const int tb = static_cast<int>(static_cast<int64_t>(blockIdx.y) * tiles / gridDim.y);       // first tile
+  const int n_qt = static_cast<int>(static_cast<int64_t>(blockIdx.y + 1) * tiles / gridDim.y);  // end
 
   // ---- K fragments (A operand): lane holds key j0 + kb*16 + c16, dims dc*32 + q4*8 ..
   const size_t kstride = static_cast<size_t>(Hkv) * D;
@@ -144,16 +152,16 @@ void mass_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[kb][i] = 0.f;
 
-  if (n_qt > 0) {
-    load_tile(0);
+  if (tb < n_qt) {
+    load_tile(tb);
     store_tile(0);
   }
   __syncthreads();
-  if (n_qt > 1) load_tile(1);
+  if (tb + 1 < n_qt) load_tile(tb + 1);
 
   auto do_tile = [&](int t, auto mask_tag) {
     constexpr bool MASK = decltype(mask_tag)::value;
-    const int cur = t & 1;
+    const int cur = (t - tb) & 1;
     const int p0 = p_begin + t * QP;
     __builtin_amdgcn_s_setprio(1);
     // scores of block nb + 1 on the matrix cores while the vector ALU turns
@@ -216,10 +224,10 @@ void mass_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
   // after its last key need no mask
   const int t_first = min(n_qt, (wave * 64) / QP);
   const int t_free = min(n_qt, (wave * 64 + 63 + QP - 1) / QP);
-  int t = 0;
+  int t = tb;
   for (; t < t_first; ++t) {  // keep the barrier rhythm of the other waves
     if (t + 1 < n_qt) {
-      store_tile((t & 1) ^ 1);
+      store_tile(((t - tb) & 1) ^ 1);
       if (t + 2 < n_qt) load_tile(t + 2);
     }
     __syncthreads();
@@ -240,7 +248,7 @@ void mass_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
       acc[kb][i] = v;
     }
   if (c16 == 0) {
-    float* mrow = mass + (static_cast<size_t>(b) * Hkv + g) * N;
+    float* mrow = mass + (static_cast<size_t>(blockIdx.y) * n_groups + grp) * N;
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
@@ -249,6 +257,34 @@ void mass_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
         if (j < N) mrow[j] = acc[kb][i];
       }
   }
+}
+
+// mass[i] = sum over p of part[p][i], in order of p
+__global__ __launch_bounds__(256) void mass_sum_kernel(const float* __restrict__ part, int64_t count, int parts,
+                                                       float* __restrict__ mass) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= count) return;
+  float x = 0.f;
+#pragma unroll 4
+  for (int p = 0; p < parts; ++p) x += part[p * count + i];
+  mass[i] = x;
+}
+
+// Workgroups per key block: about three per slot of the chip (2 per compute unit)
+// in all, so that the last ones to finish are short, each with at least 2 query
+// tiles on average (its share of the prologue and the merge). Measured, before ->
+// after: 8 prompts of 3,008 positions (768 workgroups, 2 parts) 440 -> 376 us (4
+// parts 390, 8 parts 433), one prompt of 3,008 (96, 16 parts) 256 -> 82 us, of
+// 1,000 (32, 7 parts) 93 -> 24 us, two of 8,000 (512, 3 parts) 813 -> 621 us.
+constexpr int kMassTarget = 1536, kMassPartTiles = 2, kMassMaxParts = 16;
+
+int mass_parts(const rc_shape* s) {
+  const int G = s->Hq / s->Hkv;
+  if (s->dtype != RC_BF16 || kQV % G != 0) return 1;
+  const int64_t wgs = static_cast<int64_t>(s->B) * s->Hkv * ((s->N + kMassKeys - 1) / kMassKeys);
+  const int64_t tiles = (static_cast<int64_t>(s->N) * G / kQV + 1) / 2;   // of a key block, on average
+  const int64_t p = min(min((kMassTarget + wgs - 1) / wgs, tiles / kMassPartTiles), static_cast<int64_t>(kMassMaxParts));
+  return p < 2 ? 1 : static_cast<int>(p);
 }
 
 // fp32 path: S^T = K Q^T on the matrix cores (v_mfma_f32_16x16x4_f32, fp32 in
@@ -346,9 +382,21 @@ __global__ __launch_bounds__(kMassF32Waves * 64) void mass_f32_kernel(
 }  // namespace
 }  // namespace rc
 
+extern "C" int64_t rc_mass_workspace_bytes(const rc_shape* shape) {
+  if (!shape || shape->B < 1 || shape->N < 1 || shape->Hkv < 1 || shape->Hq % shape->Hkv) return 0;
+  const int parts = rc::mass_parts(shape);
+  return parts == 1 ? 0 : static_cast<int64_t>(parts) * shape->B * shape->Hkv * shape->N * 4;
+}
+
 extern "C" int rc_attention_mass(const rc_shape* shape, const void* q, const void* k,
                                  const float* lse, float scale, float* mass,
                                  hipStream_t stream) {
+  return rc_attention_mass_ws(shape, q, k, lse, scale, mass, nullptr, 0, stream);
+}
+
+extern "C" int rc_attention_mass_ws(const rc_shape* shape, const void* q, const void* k,
+                                    const float* lse, float scale, float* mass, void* workspace,
+                                    int64_t workspace_bytes, hipStream_t stream) {
   using namespace rc;
   clear_error();
   if (int st = check_shape(shape, true)) return st;
@@ -367,15 +415,26 @@ extern "C" int rc_attention_mass(const rc_shape* shape, const void* q, const voi
     const int64_t blocks = static_cast<int64_t>(kMassXcds) * gpx * n_kblk;
     if (blocks > 0x7fffffff) return fail(RC_ERR_UNSUPPORTED, "grid too large");
     const float scale_log2e = static_cast<float>(static_cast<double>(scale) * 1.4426950408889634);
-    dim3 grid(static_cast<unsigned>(blocks));
+    const int parts = workspace && reinterpret_cast<uintptr_t>(workspace) % 4 == 0 &&
+                              workspace_bytes >= rc_mass_workspace_bytes(shape)
+                          ? mass_parts(shape)
+                          : 1;
+    float* dst = parts > 1 ? static_cast<float*>(workspace) : mass;
+    dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(parts));
     if (D == 128)
       hipLaunchKernelGGL(mass_bf16_kernel<128>, grid, dim3(kMassThreads), 0, stream,
                          static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), lse, N,
-                         Hq, Hkv, G, g_shift, scale_log2e, mass, n_kblk, n_groups, gpx);
+                         Hq, Hkv, G, g_shift, scale_log2e, dst, n_kblk, n_groups, gpx);
     else
       hipLaunchKernelGGL(mass_bf16_kernel<64>, grid, dim3(kMassThreads), 0, stream,
                          static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), lse, N,
-                         Hq, Hkv, G, g_shift, scale_log2e, mass, n_kblk, n_groups, gpx);
+                         Hq, Hkv, G, g_shift, scale_log2e, dst, n_kblk, n_groups, gpx);
+    if (parts > 1) {
+      if (int st = check_launch("rc_attention_mass")) return st;
+      const int64_t count = static_cast<int64_t>(B) * Hkv * N;
+      hipLaunchKernelGGL(mass_sum_kernel, dim3(static_cast<unsigned>((count + 255) / 256)), dim3(256), 0, stream,
+                         dst, count, parts, mass);
+    }
   } else {
     if (static_cast<int64_t>(B) * Hkv > 65535) return fail(RC_ERR_UNSUPPORTED, "B*Hkv exceeds 65535");
     dim3 grid((N + kMassF32Keys - 1) / kMassF32Keys, B * Hkv);

@@ -386,7 +386,7 @@ def selective_attention_lse(q, k, v, rows=None, scale=None, out=None, lse=None, 
 
 
 def attention_mass(q, k, lse, scale=None, mass=None, stream=None):
-    """rc_attention_mass: attention weight each key receives from every row
+    """rc_attention_mass_ws: attention weight each key receives from every row
     of its KV group's heads, [B, Hkv, N] fp32."""
     B, N, Hq, D = q.shape
     Hkv = k.shape[2]
@@ -396,9 +396,13 @@ def attention_mass(q, k, lse, scale=None, mass=None, stream=None):
         raise ValueError("lse must be fp32 [B, N, Hq] (every row of the full pass)")
     scale = 1.0 / math.sqrt(D) if scale is None else float(scale)
     mass = torch.empty((B, Hkv, N), dtype=torch.float32, device=q.device) if mass is None else mass
-    check(_lib.load().rc_attention_mass(
-        ctypes.byref(_shape(B, N, Hq, Hkv, D, _dtype_code(q))), _dev(q, "q"), _dev(k, "k"),
-        _dev(lse, "lse"), ctypes.c_float(scale), _dev(mass, "mass"), _stream(stream)))
+    lib, shape = _lib.load(), _shape(B, N, Hq, Hkv, D, _dtype_code(q))
+    nbytes = lib.rc_mass_workspace_bytes(ctypes.byref(shape))
+    ws = _workspace(nbytes, q.device, stream)
+    check(lib.rc_attention_mass_ws(
+        ctypes.byref(shape), _dev(q, "q"), _dev(k, "k"),
+        _dev(lse, "lse"), ctypes.c_float(scale), _dev(mass, "mass"),
+        None if ws is None else ws.data_ptr(), nbytes, _stream(stream)))
     return mass
 
 
