@@ -1131,7 +1131,8 @@ struct Paged {
 // workgroup, plus about 3 tiles of prologue and epilogue); splitting shortens
 // the chain and costs a second kernel and the partial outputs (fp32, written
 // and read, 66 KB per workgroup, 35 ns of the whole chip from cold memory). The
-// constants are fitted to 12 shapes x 1 .. 8 splits; a split has to promise 10%.
+// constants are fitted to 12 shapes x 1 .. 8 splits; the second kernel is priced
+// at 5 us, of which 2 are the host's, and a split has to promise 10%.
 // Measured (attention call, one request, 32 / 8 heads of 128; before -> after):
 // 344 rows of 2,080 tokens 45 -> 32 us, 506 of 3,008 61 -> 41 us, 874 of 8,160
 // 154 -> 99 us.
@@ -1147,7 +1148,7 @@ int attention_splits(const rc_shape* s, int32_t R) {
     const double tile = slots <= 0.5 ? 1.3 : slots < 1 ? 1.3 + 0.9 * (slots - 0.5) : 1.75;
     const double chain = (n / p + 3) * tile;
     const double work = wgs * (0.55 * n + 3 * p) * 1.75 / 512;   // rows see about half of the keys
-    const double us = p > 1 ? 1.1 * (max(chain, work) + 3 + 0.035 * wgs * p) : max(chain, work);
+    const double us = p > 1 ? 1.1 * (max(chain, work) + 5 + 0.035 * wgs * p) : max(chain, work);
     if (p == 1 || us < best_us) {
       best = p;
       best_us = us;

@@ -66,9 +66,17 @@ def _pool_ptr(t: torch.Tensor, name: str) -> int:
     return _dev(t, name)
 
 
-def _stream(stream=None) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+# the current stream's handle without building a Stream object around it (1 us
+# of a call that takes about 8)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(stream=None) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _shape(B, N, Hq, Hkv, D, dtype_code) -> RcShape:
@@ -335,7 +343,7 @@ def selective_attention_vref(q, k, v_ref, rows=None, scale=None, out=None, strea
     check(lib.rc_selective_attention_vref_ws(
         ctypes.byref(shape), _dev(q, "q"),
         None if rows is None else _dev(rows, "rows"), R, _dev(k, "k"), _dev(v_ref, "v_ref"),
-        ctypes.c_float(scale), _dev(out, "out"), ws_ptr, nbytes, _stream(stream)))
+        float(scale), _dev(out, "out"), ws_ptr, nbytes, _stream(stream)))
     return out
 
 
@@ -361,7 +369,7 @@ def selective_attention(q, k, v, rows=None, scale=None, out=None, stream=None,
     check(lib.rc_selective_attention_ws(
         ctypes.byref(shape), _dev(q, "q"),
         None if rows is None else _dev(rows, "rows"), R, _dev(k, "k"), _dev(v, "v"),
-        ctypes.c_float(scale), _dev(out, "out"), ws_ptr, nbytes, _stream(stream)))
+        float(scale), _dev(out, "out"), ws_ptr, nbytes, _stream(stream)))
     return out
 
 
@@ -381,7 +389,7 @@ def selective_attention_lse(q, k, v, rows=None, scale=None, out=None, lse=None, 
     check(_lib.load().rc_selective_attention_lse(
         ctypes.byref(_shape(B, N, Hq, Hkv, D, _dtype_code(q))), _dev(q, "q"),
         None if rows is None else _dev(rows, "rows"), R, _dev(k, "k"), _dev(v, "v"),
-        ctypes.c_float(scale), _dev(out, "out"), _dev(lse, "lse"), _stream(stream)))
+        float(scale), _dev(out, "out"), _dev(lse, "lse"), _stream(stream)))
     return out, lse
 
 
@@ -401,7 +409,7 @@ def attention_mass(q, k, lse, scale=None, mass=None, stream=None):
     ws = _workspace(nbytes, q.device, stream)
     check(lib.rc_attention_mass_ws(
         ctypes.byref(shape), _dev(q, "q"), _dev(k, "k"),
-        _dev(lse, "lse"), ctypes.c_float(scale), _dev(mass, "mass"),
+        _dev(lse, "lse"), float(scale), _dev(mass, "mass"),
         None if ws is None else ws.data_ptr(), nbytes, _stream(stream)))
     return mass
 
@@ -431,7 +439,7 @@ def select_tokens_eq3(segs: Segments, item_mask: int, lam: float, k_hist: int, k
         scores_out = torch.empty((B, N), dtype=torch.float32, device=k_fresh.device)
     check(_lib.load().rc_select_tokens_eq3(
         ctypes.byref(_shape(B, N, 1, Hkv, D, _dtype_code(k_fresh))), _dev(segs.dev, "segs"),
-        segs.S, segs.n_fresh, int(item_mask), ctypes.c_float(lam), int(k_hist), int(k_item),
+        segs.S, segs.n_fresh, int(item_mask), float(lam), int(k_hist), int(k_item),
         None if mass is None else _dev(mass, "mass"), _dev(k_fresh, "k_fresh"),
         _dev(v_fresh, "v_fresh"), None if k_asm is None else _dev(k_asm, "k_asm"),
         None if v_asm is None else _dev(v_asm, "v_asm"),
@@ -464,7 +472,7 @@ def paged_attention(q, k_fresh, v_fresh, pools, segs: Segments, rows, cos=None, 
         ctypes.byref(shape), _dev(q, "q"), _dev(rows, "rows"), R,
         parr, len(pools), _dev(segs.dev, "segs"), segs.S, _dev(k_fresh, "k_fresh"),
         _dev(v_fresh, "v_fresh"), None if cos is None else _dev(cos, "cos"),
-        None if sin is None else _dev(sin, "sin"), max_pos, ctypes.c_float(scale),
+        None if sin is None else _dev(sin, "sin"), max_pos, float(scale),
         _dev(out, "out"), ws_ptr, nbytes, _stream(stream)))
     return out
 
@@ -744,7 +752,7 @@ def rmsnorm(x, gamma, eps=1e-5, out=None, stream=None):
     M, Hd = x.shape
     out = torch.empty_like(x) if out is None else out
     check(_lib.load().rc_rmsnorm(int(M), int(Hd), _dev(x, "x"), _dev(gamma, "gamma"),
-                                 ctypes.c_float(eps), _dev(out, "out"), _stream(stream)))
+                                 float(eps), _dev(out, "out"), _stream(stream)))
     return out
 
 
