@@ -22,7 +22,7 @@
 //     the running denominators are column sums of the bf16 P^T taken on the
 //     matrix cores (ones x P^T), consistent with the P used for O. K/V tiles
 //     are double-buffered in LDS (one barrier per tile) with the next tile's
-//     global loads in flight during compute. For D = 128 (not paged) the
+//     global loads in flight during compute. If not paged, the
 //     tiles go from HBM straight into LDS and every K/V read of the tile loop
 //     is issued as assembly (layouts and ordering at AttnBufDirect).
 //   * A tile is computed in halves of 32 keys, so that the probabilities of
@@ -58,7 +58,7 @@ constexpr int kPagedMaxSegments = 64;  // segment table of a request kept in LDS
 using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
 using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
 
-// Row pads keep the two LDS read patterns conflict-free: 16-byte reads of 16
+// Paged: row pads keep the two LDS read patterns conflict-free: 16-byte reads of 16
 // consecutive K rows (row stride = 16 mod 256 bytes), and transposed 8-byte
 // reads of 8 consecutive V rows per half-wave (row stride = 32 mod 256 bytes).
 // Two buffers: the next tile is written while the current one is read.
@@ -68,24 +68,33 @@ struct AttnSmem {
   uint16_t v[2][kKT][D + 16];  // V tiles, key-major (read transposed)
 };
 
-// D = 128, not paged: tiles land in LDS straight from global memory
-// (global_load_lds_dwordx4: each wave instruction writes 1 KB contiguously, 4
-// whole rows of 256 bytes, the best-coalesced fetch), so rows cannot be
-// padded; the 16-byte chunks of a row are XOR-swizzled instead. K row r keeps
-// data chunk c at chunk c ^ (r % 16): a fragment read of 16 consecutive rows
-// hits 16 distinct chunks. V row r keeps data chunk c at chunk c ^ 2 (r % 8):
-// the transposed reads of one half-wave (8 consecutive rows, two adjacent
-// chunks) hit 16 distinct chunks. Every K and V read of the tile loop is
-// issued as assembly from a few precomputed per-lane addresses plus constant
+// Not paged: tiles land in LDS straight from global memory
+// (global_load_lds_dwordx4: each wave instruction writes 1 KB contiguously,
+// whole rows of 256 or 128 bytes, the best-coalesced fetch), so rows cannot be
+// padded; the 16-byte chunks of a row are XOR-swizzled instead. With D = 128, K
+// row r keeps data chunk c at chunk c ^ (r % 16): a fragment read of 16
+// consecutive rows hits 16 distinct chunks. V row r keeps data chunk c at chunk
+// c ^ 2 (r % 8): the transposed reads of one half-wave (8 consecutive rows, two
+// adjacent chunks) hit 16 distinct chunks. With D = 64 two rows share the 256
+// bytes of the banks, so the row's parity is part of the place already and the
+// swizzles take r / 2: c ^ (r / 2 % 8) and c ^ 2 (r / 2 % 4); 3 waves a SIMD
+// instead of 2 through registers and padded rows: 8 x 3,008 rows x 16 heads
+// 203 -> 169 us (full prefill), 506 rows of them 55 -> 49. Every K and V read
+// of the tile loop is issued as assembly from a few precomputed per-lane addresses plus constant
 // offsets (tile row block, buffer), and the tile loads as assembly too: the
 // compiler sees none of them, so it inserts no waits between the loads in
 // flight and the reads of the other buffer (after LDS lowering both buffers
 // are offsets of one object, and it would drain every load before each
 // read); the kernel orders them itself with explicit waits and barriers.
+template <int D>
 struct AttnBufDirect {
-  uint16_t k[kKT * 128];
-  uint16_t v[kKT * 128];
+  uint16_t k[kKT * D];
+  uint16_t v[kKT * D];
 };
+template <int D>
+__device__ __forceinline__ int k_swizzle(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
+template <int D>
+__device__ __forceinline__ int v_swizzle(int row) { return 2 * (D == 128 ? (row & 7) : ((row >> 1) & 3)); }
 struct AttnNone {
   int unused;
 };
@@ -221,12 +230,10 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
   constexpr int DC = D / 32;          // 32-wide d chunks (S^T reduction)
   constexpr int DB = D / 16;          // 16-wide d blocks (O^T rows)
   constexpr int UPR = D / 8;          // 16-byte units per K/V head row
-  constexpr int KU = kKT * UPR / kAttnThreads;   // K (and V) units per thread
-  constexpr int KSTEP = kAttnThreads / UPR;      // keys between a thread's units
-  constexpr bool DIRECT = (D == 128) && !PAGED;
-  static_assert(!VREF || DIRECT, "V rows by reference need the direct D = 128 staging");
+  constexpr bool DIRECT = !PAGED;
+  static_assert(!VREF || (DIRECT && D == 128), "V rows by reference need the direct D = 128 staging");
   __shared__ std::conditional_t<DIRECT, AttnNone, AttnSmem<D>> sm;
-  __shared__ std::conditional_t<DIRECT, AttnBufDirect, AttnNone> sbuf[2];
+  __shared__ std::conditional_t<DIRECT, AttnBufDirect<D>, AttnNone> sbuf[2];
   __shared__ int s_ext[4];
   __shared__ int4 s_psegs[PAGED ? kPagedMaxSegments : 1];
   __shared__ uint32_t s_sel[PAGED ? kMaxSelectN / 32 : 1];  // recomputed rows of the request
@@ -312,39 +319,36 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
       qf[nb][dc] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + dc * 32 + q4 * 8));
   }
 
-  // ---- K/V staging: thread owns units (key tid/UPR + i*KSTEP, dims (tid%UPR)*8 ..);
-  // paged: key pairs (key tid/PPR + i*PSTEP, dims ps*8 .. and ps*8 + D/2 ..)
+  // ---- K/V staging. Paged: a thread owns key pairs (key tid/PPR + i*PSTEP, dims
+  // col0 .. and col0 + D/2 ..)
   const size_t stride = static_cast<size_t>(Hkv) * D;   // elements between keys
   constexpr int PPR = UPR / 2;                           // pair slots per key head row
   constexpr int PSTEP = kAttnThreads / PPR;              // keys between a thread's pairs
   constexpr int PK = kKT / PSTEP;                        // key pairs per thread
-  static_assert(2 * PK == KU, "paged staging moves as many units as plain staging");
-  const int key0 = PAGED ? tid / PPR : tid / UPR;
-  const int col0 = PAGED ? (tid % PPR) * 8 : (tid % UPR) * 8;
-  const size_t off0 = (static_cast<size_t>(b) * N + key0) * stride + static_cast<size_t>(g) * D + col0;
-  const uint16_t* kp = k + off0;
-  const uint16_t* vp = v + off0;
-  const size_t tile_step = static_cast<size_t>(kKT) * stride;
-  u32x4 kreg[DIRECT ? 1 : KU], vreg[DIRECT ? 1 : KU];
+  const int key0 = tid / PPR;
+  const int col0 = (tid % PPR) * 8;
+  u32x4 kreg[PAGED ? 2 * PK : 1], vreg[PAGED ? 2 * PK : 1];
   int pdelta[PAGED ? PK : 1];  // paged: rotation of each staged key (0: none)
   int pseg[PAGED ? PK : 1] = {};  // paged: last segment starting at or before each slot's key
-  // DIRECT: wave w fills rows 16w .. 16w+15 of both tiles with 4 + 4 loads;
-  // lane l writes chunk l % 16 of row 16w + 4j + l / 16 and so fetches the
-  // data chunk that the swizzle stores there. Keys past N repeat key N - 1
+  // DIRECT: wave w fills rows 16w .. 16w+15 of both tiles with NI + NI loads of
+  // RI rows; lane l writes chunk l % UPR of row 16w + RI j + l / UPR and so
+  // fetches the data chunk that the swizzle stores there. Keys past N repeat key N - 1
   // (finite values; the causal mask removes them).
   // DIRECT, whole tiles: per-lane 32-bit byte offsets of the sources within a
   // tile, so that a tile costs one scalar base and eight loads; LDS
   // destinations derive from the wave index kept in an SGPR
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  uint32_t koff[DIRECT ? 4 : 1], voff[DIRECT ? 4 : 1];
+  constexpr int RI = 64 / UPR, NI = 16 / RI;
+  const int lch = lane % UPR;
+  uint32_t koff[DIRECT ? NI : 1], voff[DIRECT ? NI : 1];
   if constexpr (DIRECT) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = wave * 16 + j * 4 + (lane >> 4);
-      koff[j] = static_cast<uint32_t>((row * stride + g * D + (((lane & 15) ^ (row & 15)) * 8)) * 2);
-      voff[j] = static_cast<uint32_t>((row * stride + g * D + (((lane & 15) ^ (2 * (row & 7))) * 8)) * 2);
+    for (int j = 0; j < NI; ++j) {
+      const int row = wave * 16 + j * RI + lane / UPR;
+      koff[j] = static_cast<uint32_t>((row * stride + g * D + ((lch ^ k_swizzle<D>(row)) * 8)) * 2);
+      voff[j] = static_cast<uint32_t>((row * stride + g * D + ((lch ^ v_swizzle<D>(row)) * 8)) * 2);
       // VREF: the byte offset of this lane's chunk within its V row
-      if constexpr (VREF) voff[j] = static_cast<uint32_t>((g * D + (((lane & 15) ^ (2 * (row & 7))) * 8)) * 2);
+      if constexpr (VREF) voff[j] = static_cast<uint32_t>((g * D + ((lch ^ v_swizzle<D>(row)) * 8)) * 2);
     }
   }
   // VREF: v holds the address of every position's V row ([B, N], 8 bytes
@@ -384,38 +388,36 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
         const char* kt = reinterpret_cast<const char*>(k + tile0);
         const char* vt = reinterpret_cast<const char*>(v + tile0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          dma16((uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint16_t*)(&dst.k[(wave_u * 16 + j * 4) * 128])),
+        for (int j = 0; j < NI; ++j) {
+          dma16((uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint16_t*)(&dst.k[(wave_u * 16 + j * RI) * D])),
                 kt, koff[j]);
-          const uint32_t vdst = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint16_t*)(&dst.v[(wave_u * 16 + j * 4) * 128]));
+          const uint32_t vdst = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint16_t*)(&dst.v[(wave_u * 16 + j * RI) * D]));
           if constexpr (VREF) dma16_abs(vdst, reinterpret_cast<const char*>(vent[j]) + voff[j]);
           else dma16(vdst, vt, voff[j]);
         }
         return;
       }
       // the last, partial tile: keys past N repeat key N - 1
-      const int ch = lane & 15;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = wave * 16 + j * 4 + (lane >> 4);
+      for (int j = 0; j < NI; ++j) {
+        const int row = wave * 16 + j * RI + lane / UPR;
         const int key = min(t * kKT + row, N - 1);
         const uint16_t* kr = k + (static_cast<size_t>(b) * N + key) * stride + static_cast<size_t>(g) * D;
         const uint16_t* vr = v + (static_cast<size_t>(b) * N + key) * stride + static_cast<size_t>(g) * D;
         __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void*)(kr + ((ch ^ (row & 15)) * 8)),
-            (__attribute__((address_space(3))) void*)(&dst.k[(wave * 16 + j * 4) * 128]), 16, 0, 0);
+            (const __attribute__((address_space(1))) void*)(kr + ((lch ^ k_swizzle<D>(row)) * 8)),
+            (__attribute__((address_space(3))) void*)(&dst.k[(wave * 16 + j * RI) * D]), 16, 0, 0);
         if constexpr (VREF)
-          dma16_abs((uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint16_t*)(&dst.v[(wave_u * 16 + j * 4) * 128])),
+          dma16_abs((uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint16_t*)(&dst.v[(wave_u * 16 + j * RI) * D])),
                     reinterpret_cast<const char*>(vent[j]) + voff[j]);
         else
           __builtin_amdgcn_global_load_lds(
-              (const __attribute__((address_space(1))) void*)(vr + ((ch ^ (2 * (row & 7))) * 8)),
-              (__attribute__((address_space(3))) void*)(&dst.v[(wave * 16 + j * 4) * 128]), 16, 0, 0);
+              (const __attribute__((address_space(1))) void*)(vr + ((lch ^ v_swizzle<D>(row)) * 8)),
+              (__attribute__((address_space(3))) void*)(&dst.v[(wave * 16 + j * RI) * D]), 16, 0, 0);
       }
     }
   };
   auto load_tile = [&](int t) {
-    if constexpr (!DIRECT) {
     if constexpr (PAGED) {
 #pragma unroll
       for (int i = 0; i < PK; ++i) {
@@ -451,28 +453,9 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
         vreg[2 * i] = vs ? *reinterpret_cast<const u32x4*>(vs) : u32x4{0, 0, 0, 0};
         vreg[2 * i + 1] = vs ? *reinterpret_cast<const u32x4*>(vs + D / 2) : u32x4{0, 0, 0, 0};
       }
-      return;
     }
-    const uint16_t* kt = kp + t * tile_step;
-    const uint16_t* vt = vp + t * tile_step;
-    if ((t + 1) * kKT <= N) {
-#pragma unroll
-      for (int i = 0; i < KU; ++i) {
-        kreg[i] = *reinterpret_cast<const u32x4*>(kt + i * KSTEP * stride);
-        vreg[i] = *reinterpret_cast<const u32x4*>(vt + i * KSTEP * stride);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < KU; ++i) {
-        const bool in = t * kKT + key0 + i * KSTEP < N;
-        kreg[i] = in ? *reinterpret_cast<const u32x4*>(kt + i * KSTEP * stride) : u32x4{0, 0, 0, 0};
-        vreg[i] = in ? *reinterpret_cast<const u32x4*>(vt + i * KSTEP * stride) : u32x4{0, 0, 0, 0};
-      }
-    }
-      }
-};
+  };
   auto store_tile = [&](int buf) {
-    if constexpr (!DIRECT) {
     if constexpr (PAGED) {
 #pragma unroll
       for (int i = 0; i < PK; ++i) {
@@ -494,15 +477,8 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
         *reinterpret_cast<u32x4*>(&sm.v[buf][key][col0]) = vreg[2 * i];
         *reinterpret_cast<u32x4*>(&sm.v[buf][key][col0 + D / 2]) = vreg[2 * i + 1];
       }
-      return;
     }
-#pragma unroll
-    for (int i = 0; i < KU; ++i) {
-      *reinterpret_cast<u32x4*>(&sm.k[buf][key0 + i * KSTEP][col0]) = kreg[i];
-      *reinterpret_cast<u32x4*>(&sm.v[buf][key0 + i * KSTEP][col0]) = vreg[i];
-    }
-      }
-};
+  };
 
   f32x4 o[DB][2];
 #pragma unroll
@@ -534,22 +510,22 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
     if constexpr (DIRECT) return nullptr;   // DIRECT reads V through vaddr below
     else return &sm.v[BUF][row][col];
   };
-  // DIRECT: LDS byte address of this lane's 8 bytes in the first V block
   // DIRECT: LDS byte address of this lane's transposed V read of 16-dim block
   // db in rows 4 q4 + c16/4 (+ a multiple of 16 rows, a constant offset)
   uint32_t vaddr[DIRECT ? DB : 1], kaddr[DIRECT ? DC : 1];
   if constexpr (DIRECT) {
     const uint32_t v0 = (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) uint16_t*)(&sbuf[0].v[0]));
     const uint32_t k0 = (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) uint16_t*)(&sbuf[0].k[0]));
-    const int x = 4 * (q4 & 1) + (c16 >> 2);   // row % 8 of this lane's rows
-    const uint32_t lane_part = (4 * q4 + (c16 >> 2)) * 256 + (c16 & 1) * 8;
+    const int vrow = 4 * q4 + (c16 >> 2);   // this lane's rows are vrow + a multiple of 16
 #pragma unroll
-    for (int db = 0; db < DB; ++db) vaddr[db] = v0 + lane_part + (2 * (db ^ x) + ((c16 >> 1) & 1)) * 16;
-    // K fragment (kb, dc): row kb*16 + c16, data chunk dc*4 + q4 at chunk (dc*4 + q4) ^ c16
+    for (int db = 0; db < DB; ++db)
+      vaddr[db] = v0 + vrow * (2 * D) + ((2 * db + ((c16 >> 1) & 1)) ^ v_swizzle<D>(vrow)) * 16 + (c16 & 1) * 8;
+    // K fragment (kb, dc): row kb*16 + c16, data chunk dc*4 + q4
 #pragma unroll
-    for (int dc = 0; dc < DC; ++dc) kaddr[dc] = k0 + c16 * 256 + (((dc * 4 + q4) ^ c16) * 16);
+    for (int dc = 0; dc < DC; ++dc) kaddr[dc] = k0 + c16 * (2 * D) + (((dc * 4 + q4) ^ k_swizzle<D>(c16)) * 16);
   }
-  constexpr uint32_t kBufBytes = sizeof(AttnBufDirect);
+  constexpr uint32_t kBufBytes = sizeof(AttnBufDirect<D>);
+  constexpr uint32_t k16Rows = 16 * 2 * D;   // bytes of 16 tile rows
   using Buf0 = std::integral_constant<int, 0>;
   using Buf1 = std::integral_constant<int, 1>;
 
@@ -598,7 +574,7 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
       constexpr int gi = decltype(G)::value;
       constexpr int h = gi / (KG / 2), r = gi % (KG / 2);
       constexpr int kb = 2 * h + r % 2, dc = r / 2;
-      kf[gi] = lds_read_b128_async<cur * kBufBytes + kb * 4096>(kaddr[dc]);
+      kf[gi] = lds_read_b128_async<cur * kBufBytes + kb * k16Rows>(kaddr[dc]);
     };
     auto mm = [&](auto G) {
       constexpr int gi = decltype(G)::value;
@@ -715,8 +691,8 @@ void attn_bf16_kernel(const uint16_t* __restrict__ q, const int32_t* __restrict_
     auto rd = [&](auto G) {
       constexpr int gi = decltype(G)::value;
       constexpr int kc = gi / DB, db = gi % DB;
-      lo[gi] = lds_read_tr4_async<cur * kBufBytes + kc * 8192>(vaddr[db]);
-      hi[gi] = lds_read_tr4_async<cur * kBufBytes + kc * 8192 + 4096>(vaddr[db]);
+      lo[gi] = lds_read_tr4_async<cur * kBufBytes + kc * 2 * k16Rows>(vaddr[db]);
+      hi[gi] = lds_read_tr4_async<cur * kBufBytes + kc * 2 * k16Rows + k16Rows>(vaddr[db]);
     };
     auto pv = [&](auto G) {
       constexpr int gi = decltype(G)::value;
